@@ -1,0 +1,81 @@
+"""The logits pass at the edges of its block shapes: rows that just fit one tile
+a wave and that just do not, four- and eight-wave blocks, rows split over blocks,
+misaligned rows, and rows of equal logits, whose candidates overflow the block's
+list.  Against float64 sums and a sort by (logit descending, id ascending).
+
+Tolerances: ids exact.  log q, lse and the entropy are fp64 sums of fp32
+exponentials (2^-22 relative each) rounded to fp32; 1e-5 relative with a floor of
+1e-6 is the bound of the parity tests."""
+import numpy as np
+import pytest
+
+torch = pytest.importorskip("torch")
+
+pytestmark = pytest.mark.gpu
+
+SHAPES = [
+    # batch, L, V, K, kind
+    (1, 1, 5, 5, "normal"),             # no vector at all: only loose elements
+    (1, 3, 16384, 4, "normal"),         # 8 waves, exactly one tile a wave
+    (1, 3, 16391, 13, "normal"),        # one vector fewer or the same, misaligned
+    (2, 3, 16400, 64, "normal"),        # two vectors more: the streaming kernel
+    (1, 2, 18433, 33, "normal"),        # the ninth tile
+    (1, 64, 98312, 8, "normal"),        # 64 rows above the split line: 4 blocks a row
+    (5, 13, 98312, 8, "normal"),        # one row more: not split
+    (1, 4, 98304, 8, "normal"),         # at the line: not split
+    (1, 3, 98311, 32, "normal"),        # split, misaligned, last split short
+    (1, 1, 151937, 64, "normal"),       # the most splits a row of this size takes
+    (1, 5, 300007, 64, "normal"),       # 32 blocks a row at most
+    (32, 16, 4100, 16, "normal"),       # 512 rows: 8 waves
+    (27, 19, 8201, 16, "normal"),       # 513 rows: 4 waves, just past one tile a wave
+    (27, 19, 8191, 40, "normal"),       # 513 rows: 4 waves, at most one tile a wave
+    (1, 2, 16000, 16, "equal"),         # one value: 16000 candidates tie
+    (1, 2, 40000, 64, "equal"),
+    (27, 19, 9000, 5, "equal"),
+    (1, 2, 120000, 48, "equal"),        # split: every partial list is a tie
+    (1, 3, 20011, 64, "levels"),        # four values only
+    (1, 3, 120011, 17, "levels"),
+]
+
+
+def draw(kind, rows, V, seed):
+    g = np.random.default_rng(seed)
+    if kind == "equal":
+        x = np.full((rows, V), -1.5, np.float32)
+    elif kind == "levels":
+        x = g.integers(-2, 2, (rows, V)).astype(np.float32)
+    else:
+        x = g.standard_normal((rows, V), dtype=np.float32) * 3
+    return torch.from_numpy(x).to(torch.bfloat16)
+
+
+@pytest.mark.parametrize("batch,L,V,K,kind", SHAPES)
+@pytest.mark.parametrize("static", [False, True])
+def test_logits_shapes(batch, L, V, K, kind, static):
+    import paper_2608_20375_amd as G
+    print("batch", batch, "L", L, "V", V, "K", K, kind, static, flush=True)
+    rows = batch * L
+    x = draw(kind, rows, V, 77 + V + K).cuda()
+    ctx = G.Context(batch, L, V, K, 8)
+    emb = torch.zeros(V, 4, device="cuda")
+    g = torch.zeros(4, 4, device="cuda")
+    ctx.set_scorer(emb, g, g)
+    zeros = torch.zeros(batch, dtype=torch.int32, device="cuda")
+    out = ctx.build_tree(x.view(batch, L, V), zeros, zeros, fixed_budget=zeros + 1,
+                         static_scratch=static)
+    d = x.double()
+    lse = torch.logsumexp(d, -1)
+    lp = d - lse[:, None]
+    # stable: equal logits keep ascending ids
+    want = torch.sort(x.float(), dim=-1, descending=True, stable=True).indices[:, :K]
+    assert torch.equal(out.topk_ids.view(rows, K).long(), want)
+    # float64 reference, copied to the host
+    for got, ref in ((out.topk_logq.view(rows, K), lp.gather(-1, want)),
+                     (out.row_lse.view(rows), lse),
+                     (out.row_maxprob.view(rows), lp.max(-1).values.exp()),
+                     (out.row_entropy.view(rows), -(lp.exp() * lp).sum(-1))):
+        ref = ref.cpu().numpy()
+        err = np.abs(got.double().cpu().numpy() - ref)
+        assert (err <= 1e-6 + 1e-5 * np.abs(ref)).all()
+    assert ctx.device_status() == 0
+    ctx.close()
