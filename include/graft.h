@@ -445,8 +445,8 @@ typedef struct {
  *   tau_t = max(phi . [1, s_t], tau_min),
  * with each round's scale A_t eliminated in closed form (it cancels in the
  * budget rule's argmax); rounds that accept nothing contribute nothing.  The
- * sums over the log run on the device (fp64, fixed order: deterministic), the
- * 4 x 4 steps on the host; synchronous on `stream`.  phi_out and c_out (host,
+ * sums over the log and the steps run on the device (fp64, fixed order:
+ * deterministic); synchronous on `stream`.  phi_out and c_out (host,
  * 4 and 3 floats) are graft_saba_desc's phi and c0..c2; stats (host, 4 doubles,
  * or NULL): the gain and cost sums of squares, the iterations taken, and 1 if
  * the steps converged (0 if max_iter ran out or the system was singular, e.g.

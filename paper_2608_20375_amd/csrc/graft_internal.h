@@ -16,7 +16,7 @@ constexpr int kMaxGrid = 64;
 constexpr int kMaxScoreDim = 64;
 constexpr int kTdesMaxLossBlocks = 512;
 constexpr int kFitSums = 25;        // replay sums: SSE, J^T J (10), J^T r (4), X^T X (6), X^T y (3), y^T y
-constexpr int kFitMaxBlocks = 1024;
+constexpr int kFitMaxBlocks = 256;
 constexpr int kReadSinkWords = GRAFT_READ_STREAM_SINK_WORDS;
 
 // ---------------------------------------------------------------------------
@@ -331,14 +331,19 @@ hipError_t launch_tdes_step(graft_tdes *t, const float *emb, const graft_tdes_ba
                             const graft_tdes_hyper *h, int32_t step, float *theta, float *m1,
                             float *m2, double *loss, float *grad, hipStream_t stream);
 
-// SABA fit: the replay sums at phi (kFitSums doubles into out, device), with
-// the cost's normal equations (with_cost 1) or the residual sum of squares of
-// cost c (with_cost 2); partial holds kFitMaxBlocks * kFitSums doubles.
-int saba_fit_blocks(int T);
-hipError_t launch_replay_sums(int T, int nb, const int32_t *budgets, const float *state,
-                              const int32_t *prefix, const float *accepted, const float *latency,
-                              const double phi[4], double tau_min, int with_cost,
-                              const double c[3], double *partial, double *out, hipStream_t stream);
+// SABA fit: a queue of launches 0, 1, 2, ... on one stream, each an evaluation of
+// the log and the step before it; *state (device) is the state that launch i has
+// stored, its point the best of the evaluations of the launches before i.  work
+// holds saba_fit_bytes() bytes, 16-byte aligned, and needs no clearing.
+struct FitState {
+  double phi[4], trial[4], d[4];   // best point, point under evaluation, step to it
+  double F, H[10], g[4], lam;      // at phi
+  double c[3], cost_sse;
+  int32_t iters, converged, done, cost_ok;
+};
+int64_t saba_fit_bytes();
+hipError_t launch_saba_fit(const graft_saba_replay *log, const float *phi_init, int max_iter,
+                           void *work, int launch, FitState **state, hipStream_t stream);
 
 // Plain read of bytes (a multiple of 16) at src (16-byte aligned); the sink
 // holds kReadSinkWords words.
