@@ -30,6 +30,7 @@ EXPORTED_SYMBOLS = (
 )
 
 READ_STREAM_SINK_WORDS = 4096
+_BF16_BITS = (torch.bfloat16, torch.int16, torch.uint16)   # dtypes that hold bf16 bit patterns
 
 
 class GraftError(RuntimeError):
@@ -196,6 +197,20 @@ def _need(t, name, *dims):
         raise ValueError("%s must be [%s], got %s" % (name, want, list(t.shape)))
 
 
+def _plain(t, dtype, shape):
+    """Device pointer of a tensor that is exactly what a call takes: on the GPU,
+    contiguous, of this dtype and shape; None for None.  Anything else gives -1,
+    and the caller goes through _need and _ptr, which accept what else the call
+    allows or raise.  A call passes a dozen tensors, and at small batches the
+    round waits for the host: this check takes a third of their time."""
+    if t is None:
+        return None
+    if (isinstance(t, torch.Tensor) and t.is_cuda and t.dtype is dtype and t.shape == shape
+            and t.is_contiguous()):
+        return t.data_ptr()
+    return -1
+
+
 def _batch_of(t, name):
     if not isinstance(t, torch.Tensor) or t.dim() < 1:
         raise ValueError("%s must be a tensor whose first extent is the batch" % name)
@@ -204,6 +219,13 @@ def _batch_of(t, name):
 
 def _stream():
     return torch.cuda.current_stream().cuda_stream
+
+
+# The current stream's handle without the Stream object around it, where this
+# torch offers it (1.3 us a call less).
+if hasattr(torch._C, "_cuda_getCurrentRawStream"):
+    def _stream():  # noqa: F811
+        return torch._C._cuda_getCurrentRawStream(torch.cuda.current_device())
 
 
 def _check(status: int, where: str):
@@ -327,6 +349,51 @@ class Context:
         states; with them the SABA state uses the degeneration signal.
         static_scratch: call graft_build_tree_static (no device allocation in the
         library; pass preallocated `out` to allocate nothing here either)."""
+        r = self._round_plain(logits, root_token, base_pos, prefix_len, hist, fixed_budget, hidden,
+                              out)
+        if r is None:
+            r, out = self._round_checked(logits, root_token, base_pos, prefix_len, hist,
+                                         fixed_budget, hidden, out, want)
+        L = lib()
+        if static_scratch:
+            _check(L.graft_build_tree_static(self._h, C.byref(r), C.byref(out._struct), _stream()),
+                   "graft_build_tree_static")
+        else:
+            _check(L.graft_build_tree(self._h, C.byref(r), C.byref(out._struct), _stream()),
+                   "graft_build_tree")
+        return out
+
+    def _round_plain(self, logits, root_token, base_pos, prefix_len, hist, fixed_budget, hidden,
+                     out):
+        """The round's inputs when every tensor is plain and out fits; else None."""
+        dm = self.dims
+        L, V = dm.num_pos, dm.vocab
+        if (out is None or out.sizes != (L, dm.top_k, dm.max_nodes) or not isinstance(logits, torch.Tensor)
+                or logits.dim() != 3 or root_token is None or base_pos is None):
+            return None
+        shape = logits.shape
+        batch = shape[0]
+        if out.batch < batch or shape[1] != L or shape[2] != V:
+            return None
+        one = (batch,)
+        i32 = torch.int32
+        H = 0
+        p_hid = None
+        if hidden is not None:
+            if not isinstance(hidden, torch.Tensor) or hidden.dim() != 3 or hidden.shape[2] < 1:
+                return None
+            H = hidden.shape[2]
+            p_hid = _plain(hidden, hidden.dtype if hidden.dtype in _BF16_BITS else None,
+                           (batch, L, H))
+        p = (_plain(logits, logits.dtype if logits.dtype in _BF16_BITS else None, shape),
+             _plain(root_token, i32, one), _plain(base_pos, i32, one), _plain(prefix_len, i32, one),
+             _plain(hist, torch.float32, one), _plain(fixed_budget, i32, one), p_hid)
+        if -1 in p:
+            return None
+        return RoundIn(batch, *p, H)
+
+    def _round_checked(self, logits, root_token, base_pos, prefix_len, hist, fixed_budget, hidden,
+                       out, want):
         dm = self.dims
         batch = _batch_of(logits, "logits")
         _need(logits, "logits", batch, dm.num_pos, dm.vocab)
@@ -351,12 +418,33 @@ class Context:
                     _ptr(prefix_len, torch.int32, "prefix_len"), _ptr(hist, torch.float32, "hist"),
                     _ptr(fixed_budget, torch.int32, "fixed_budget"), _ptr(hidden, None, "hidden"),
                     0 if hidden is None else int(hidden.shape[-1]))
-        fn = "graft_build_tree_static" if static_scratch else "graft_build_tree"
-        _check(getattr(lib(), fn)(self._h, C.byref(r), C.byref(out._struct), _stream()), fn)
-        return out
+        return r, out
 
     def accept(self, n_nodes, tokens, parents, target_root=None, target_node=None,
                target_depth=None, update_history=False, acc_len=None, acc_nodes=None, bonus=None):
+        p = None
+        if (acc_len is not None and acc_nodes is not None and bonus is not None
+                and isinstance(n_nodes, torch.Tensor) and n_nodes.dim() == 1
+                and tokens is not None and parents is not None):
+            L, N = self.dims.num_pos, self.dims.max_nodes
+            batch = n_nodes.shape[0]
+            i32 = torch.int32
+            one, row = (batch,), (batch, N)
+            p = (_plain(target_root, i32, one), _plain(target_node, i32, row),
+                 _plain(target_depth, i32, (batch, L + 1)), _plain(n_nodes, i32, one),
+                 _plain(tokens, i32, row), _plain(parents, i32, row), _plain(acc_len, i32, one),
+                 _plain(acc_nodes, i32, (batch, L)), _plain(bonus, i32, one))
+        if p is None or -1 in p:
+            batch, p, acc_len, acc_nodes, bonus = self._accept_checked(
+                n_nodes, tokens, parents, target_root, target_node, target_depth, acc_len,
+                acc_nodes, bonus)
+        t = Targets(p[0], p[1], p[2])
+        _check(lib().graft_accept(self._h, batch, p[3], p[4], p[5], C.byref(t), p[6], p[7], p[8],
+                                  1 if update_history else 0, _stream()), "graft_accept")
+        return acc_len, acc_nodes, bonus
+
+    def _accept_checked(self, n_nodes, tokens, parents, target_root, target_node, target_depth,
+                        acc_len, acc_nodes, bonus):
         dm = self.dims
         batch = _batch_of(n_nodes, "n_nodes")
         _need(n_nodes, "n_nodes", batch)
@@ -373,17 +461,13 @@ class Context:
         acc_nodes = (torch.empty(batch, self.dims.num_pos, dtype=torch.int32, device=dev)
                      if acc_nodes is None else acc_nodes)
         bonus = torch.empty(batch, dtype=torch.int32, device=dev) if bonus is None else bonus
-        t = Targets(_ptr(target_root, torch.int32, "target_root"),
-                    _ptr(target_node, torch.int32, "target_node"),
-                    _ptr(target_depth, torch.int32, "target_depth"))
-        _check(lib().graft_accept(self._h, batch, _ptr(n_nodes, torch.int32, "n_nodes"),
-                                  _ptr(tokens, torch.int32, "tokens"),
-                                  _ptr(parents, torch.int32, "parents"), C.byref(t),
-                                  _ptr(acc_len, torch.int32, "acc_len"),
-                                  _ptr(acc_nodes, torch.int32, "acc_nodes"),
-                                  _ptr(bonus, torch.int32, "bonus"), int(bool(update_history)),
-                                  _stream()), "graft_accept")
-        return acc_len, acc_nodes, bonus
+        p = (_ptr(target_root, torch.int32, "target_root"),
+             _ptr(target_node, torch.int32, "target_node"),
+             _ptr(target_depth, torch.int32, "target_depth"),
+             _ptr(n_nodes, torch.int32, "n_nodes"), _ptr(tokens, torch.int32, "tokens"),
+             _ptr(parents, torch.int32, "parents"), _ptr(acc_len, torch.int32, "acc_len"),
+             _ptr(acc_nodes, torch.int32, "acc_nodes"), _ptr(bonus, torch.int32, "bonus"))
+        return batch, p, acc_len, acc_nodes, bonus
 
     def synth_node_targets(self, seed, root_token, n_nodes, tokens, parents, topk_ids,
                            target_root=None, target_node=None):
@@ -416,21 +500,27 @@ class Context:
         bias); allocated as [batch, max_nodes, max_nodes] when None."""
         batch = _batch_of(n_nodes, "n_nodes")
         N = self.dims.max_nodes
-        _need(n_nodes, "n_nodes", batch)
-        _need(mask, "mask", (batch,), N, (N + 63) // 64)
+        p_n = _plain(n_nodes, torch.int32, (batch,))
+        p_mask = _plain(mask, torch.int64, (batch, N, (N + 63) // 64))
+        if p_n in (None, -1) or p_mask in (None, -1):
+            _need(n_nodes, "n_nodes", batch)
+            _need(mask, "mask", (batch,), N, (N + 63) // 64)
         if bias is None:
             bias = torch.empty(batch, N, N, dtype=dtype, device=n_nodes.device)
         if bias.dtype not in (torch.float32, torch.bfloat16):
             raise TypeError("bias must be float32 or bfloat16")
-        if bias.dim() != 3 or bias.shape[0] < batch or bias.shape[1] < N or bias.shape[2] < N:
+        shape = bias.shape
+        if len(shape) != 3 or shape[0] < batch or shape[1] < N or shape[2] < N:
             raise ValueError("bias must be at least [batch, max_nodes, max_nodes]")
-        if bias.stride(2) != 1:
+        step = bias.stride()
+        if step[2] != 1:
             raise ValueError("bias must have unit stride along its last dimension")
-        _check(lib().graft_mask_to_bias(self._h, batch, _ptr(n_nodes, torch.int32, "n_nodes"),
-                                        _ptr(mask, torch.int64, "mask"), bias.data_ptr(),
-                                        1 if bias.dtype == torch.bfloat16 else 0,
-                                        bias.stride(1), bias.stride(0), _stream()),
-               "graft_mask_to_bias")
+        if p_n in (None, -1) or p_mask in (None, -1):
+            p_n = _ptr(n_nodes, torch.int32, "n_nodes")
+            p_mask = _ptr(mask, torch.int64, "mask")
+        _check(lib().graft_mask_to_bias(self._h, batch, p_n, p_mask, bias.data_ptr(),
+                                        1 if bias.dtype == torch.bfloat16 else 0, step[1], step[0],
+                                        _stream()), "graft_mask_to_bias")
         return bias
 
     def commit_accepted(self, acc_len, acc_nodes, src, dst=None):
@@ -439,25 +529,35 @@ class Context:
         dst defaults to src (compaction in place)."""
         dst = src if dst is None else dst
         batch = _batch_of(acc_len, "acc_len")
-        _need(acc_len, "acc_len", batch)
-        _need(acc_nodes, "acc_nodes", (batch,), self.dims.num_pos)
+        dm = self.dims
+        L, N = dm.num_pos, dm.max_nodes
+        p_len = _plain(acc_len, torch.int32, (batch,))
+        p_nodes = _plain(acc_nodes, torch.int32, (batch, L))
+        if p_len in (None, -1) or p_nodes in (None, -1):
+            _need(acc_len, "acc_len", batch)
+            _need(acc_nodes, "acc_nodes", (batch,), L)
         # node indices reach max_nodes - 1 in src; at most L rows are written in dst
-        _need(src, "src", (1,), (batch,), (self.dims.max_nodes,), (1,))
-        _need(dst, "dst", (1,), (batch,), (self.dims.num_pos,), (1,))
+        for name, t, rows in (("src", src, N), ("dst", dst, L)):
+            if not (isinstance(t, torch.Tensor) and t.dim() == 4 and min(t.shape) >= 1
+                    and t.shape[1] >= batch and t.shape[2] >= rows):
+                _need(t, name, (1,), (batch,), (rows,), (1,))
         for name, t in (("src", src), ("dst", dst)):
-            if t.device.type != "cuda":
+            if not t.is_cuda:
                 raise TypeError("%s must be a CUDA (HIP) tensor [planes, batch, rows, width]" % name)
             if t.stride(3) != 1:
                 raise ValueError("%s must have unit stride along its last dimension" % name)
-        if src.dtype != dst.dtype or src.shape[0] != dst.shape[0] or src.shape[3] != dst.shape[3]:
+        planes, _, _, width = src.shape
+        ss, ds = src.stride(), dst.stride()
+        if src.dtype != dst.dtype or planes != dst.shape[0] or width != dst.shape[3]:
             raise ValueError("src and dst must agree in dtype, planes and width")
+        if p_len in (None, -1) or p_nodes in (None, -1):
+            p_len = _ptr(acc_len, torch.int32, "acc_len")
+            p_nodes = _ptr(acc_nodes, torch.int32, "acc_nodes")
         es = src.element_size()
         _check(lib().graft_commit_accepted(
-            self._h, batch, _ptr(acc_len, torch.int32, "acc_len"),
-            _ptr(acc_nodes, torch.int32, "acc_nodes"), src.data_ptr(), dst.data_ptr(),
-            src.shape[3] * es, src.shape[0], src.stride(0) * es, src.stride(1) * es,
-            src.stride(2) * es, dst.stride(0) * es, dst.stride(1) * es, dst.stride(2) * es,
-            _stream()), "graft_commit_accepted")
+            self._h, batch, p_len, p_nodes, src.data_ptr(), dst.data_ptr(), width * es, planes,
+            ss[0] * es, ss[1] * es, ss[2] * es, ds[0] * es, ds[1] * es, ds[2] * es, _stream()),
+            "graft_commit_accepted")
         return dst
 
     def profile_begin(self, max_calls: int):
@@ -513,6 +613,40 @@ class TdesTrainer:
         """One step on `batch` (CUDA tensors: parent, depth, target int32 [G]; child
         int32 [G, K]; logq, z float32 [G, K]; pairs int32 [P, 6]).  Updates theta,
         adam_m, adam_v in place; writes loss (float64 [4]) and grad when given."""
+        p = self._step_plain(emb, batch, theta, adam_m, adam_v, loss, grad)
+        if p is None:
+            p = self._step_checked(emb, batch, theta, adam_m, adam_v, loss, grad)
+        b, p_emb, p_theta, p_m, p_v, p_loss, p_grad = p
+        h = hyper if hyper is not None else TdesHyper()
+        _check(lib().graft_tdes_step(self._h, p_emb, C.byref(b), C.byref(h), int(step), p_theta, p_m,
+                                     p_v, p_loss, p_grad, _stream()), "graft_tdes_step")
+
+    def _step_plain(self, emb, batch, theta, adam_m, adam_v, loss, grad):
+        """The step's arguments when every tensor is plain; else None."""
+        if type(batch) is not dict:
+            return None
+        d = self.dims
+        i32, f32, f64 = torch.int32, torch.float32, torch.float64
+        child, pairs = batch.get("child"), batch.get("pairs")
+        if (not isinstance(child, torch.Tensor) or child.dim() != 2
+                or not isinstance(pairs, torch.Tensor) or pairs.dim() != 2):
+            return None
+        G, P = child.shape[0], pairs.shape[0]
+        if G < 1 or P < 1:
+            return None
+        K, n = d.top_k, (self.param_count,)
+        per, one = (G, K), (G,)
+        g = (_plain(batch.get("parent"), i32, one), _plain(batch.get("depth"), i32, one),
+             _plain(child, i32, per), _plain(batch.get("logq"), f32, per),
+             _plain(batch.get("z"), f32, per), _plain(batch.get("target"), i32, one))
+        p = (_plain(emb, f32, (d.vocab, d.emb_dim)), _plain(theta, f32, n), _plain(adam_m, f32, n),
+             _plain(adam_v, f32, n))
+        q = (_plain(pairs, i32, (P, 6)), _plain(loss, f64, (4,)), _plain(grad, f32, n))
+        if -1 in g or None in g or -1 in p or None in p or -1 in q:
+            return None
+        return (TdesBatch(G, *g, P, q[0]), *p, q[1], q[2])
+
+    def _step_checked(self, emb, batch, theta, adam_m, adam_v, loss, grad):
         d = self.dims
         G = int(batch["child"].shape[0]) if "child" in batch else 0
         P = int(batch["pairs"].shape[0]) if "pairs" in batch else 0
@@ -542,12 +676,9 @@ class TdesTrainer:
             raise ValueError("emb must be [%d, %d]" % (d.vocab, d.emb_dim))
         if loss is not None and (loss.dtype != torch.float64 or loss.numel() < 4):
             raise ValueError("loss must be float64 with 4 entries")
-        h = hyper if hyper is not None else TdesHyper()
-        _check(lib().graft_tdes_step(self._h, _ptr(emb, f32, "emb"), C.byref(b), C.byref(h),
-                                     int(step), _ptr(theta, f32, "theta"),
-                                     _ptr(adam_m, f32, "adam_m"), _ptr(adam_v, f32, "adam_v"),
-                                     _ptr(loss, torch.float64, "loss"), _ptr(grad, f32, "grad"),
-                                     _stream()), "graft_tdes_step")
+        return (b, _ptr(emb, f32, "emb"), _ptr(theta, f32, "theta"), _ptr(adam_m, f32, "adam_m"),
+                _ptr(adam_v, f32, "adam_v"), _ptr(loss, torch.float64, "loss"),
+                _ptr(grad, f32, "grad"))
 
     def device_status(self) -> int:
         return lib().graft_tdes_device_status(self._h, _stream())
