@@ -659,11 +659,15 @@ int graft_tdes_create(const graft_tdes_dims *dims, graft_tdes **out) {
   if (!t) return fail(GRAFT_ERR_OUT_OF_MEMORY, "graft_tdes_create: host allocation failed");
   t->dims = d;
   const graft::TdesWorkspace ws = graft::tdes_workspace(d);
-  hipError_t e = dalloc(&t->dyc, static_cast<size_t>(ws.dyc));
-  if (e == hipSuccess) e = dalloc(&t->dyp, static_cast<size_t>(ws.dyp));
-  if (e == hipSuccess) e = dalloc(&t->part_u, static_cast<size_t>(ws.part_u));
+  // the fp32 parts in one allocation, each a multiple of 64 entries
+  hipError_t e = dalloc(&t->dyc, static_cast<size_t>(ws.dyc + ws.dyp + ws.wsum + ws.part_u + ws.part_w));
+  if (e == hipSuccess) {
+    t->dyp = t->dyc + ws.dyc;
+    t->wsum = t->dyp + ws.dyp;
+    t->part_u = t->wsum + ws.wsum;
+    t->part_w = t->part_u + ws.part_u;
+  }
   if (e == hipSuccess) e = dalloc(&t->part_d, static_cast<size_t>(ws.part_d));
-  if (e == hipSuccess) e = dalloc(&t->part_w, static_cast<size_t>(ws.part_w));
   if (e == hipSuccess) e = dalloc(&t->error_flag, 1);
   if (e == hipSuccess) e = hipMemset(t->error_flag, 0, sizeof(uint32_t));
   if (e != hipSuccess) {
@@ -680,10 +684,7 @@ void graft_tdes_destroy(graft_tdes *t) {
   if (!t) return;
   (void)hipDeviceSynchronize();
   (void)hipFree(t->dyc);
-  (void)hipFree(t->dyp);
-  (void)hipFree(t->part_u);
   (void)hipFree(t->part_d);
-  (void)hipFree(t->part_w);
   (void)hipFree(t->error_flag);
   delete t;
 }

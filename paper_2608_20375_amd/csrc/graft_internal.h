@@ -14,7 +14,7 @@ constexpr int kMaxK = 64;
 constexpr int kMaxNodes = 1024;
 constexpr int kMaxGrid = 64;
 constexpr int kMaxScoreDim = 64;
-constexpr int kTdesMaxLossBlocks = 512;
+constexpr int kTdesMaxLossBlocks = 1024;   // a power of two
 constexpr int kFitSums = 25;        // replay sums: SSE, J^T J (10), J^T r (4), X^T X (6), X^T y (3), y^T y
 constexpr int kFitMaxBlocks = 256;
 constexpr int kReadSinkWords = GRAFT_READ_STREAM_SINK_WORDS;
@@ -272,8 +272,10 @@ struct graft_ctx {
 
 struct graft_tdes {
   graft_tdes_dims dims;
-  float *dyc;              // [max_groups K + 2 max_pairs, M16] dL/db of the child-tower rows
+  float *dyc;              // [max_groups + 2 max_pairs, M16] dL/db of the pairs' child-tower rows
+                           // (a group: its parent tower, see wsum)
   float *dyp;              // [max_groups + 2 max_pairs, M16] dL/da of the parent-tower rows
+  float *wsum;             // [max_groups, E] sum of a group's child rows weighted by dL/df
   float *part_u;           // depth-embedding gradient partials of the loss blocks
   double *part_d;          // [kTdesMaxLossBlocks, 4] scale gradient and objective sums
   float *part_w;           // projection gradient partials of the wgrad blocks
@@ -319,11 +321,11 @@ hipError_t launch_synth_targets(graft_ctx *ctx, int batch, uint64_t seed,
 // TDES training step: launch sizes for a batch, the instantiated shapes, and
 // the three launches (loss_kernel, wgrad_kernel, update_kernel).
 struct TdesPlan {
-  int loss_blocks, child_blocks, parent_blocks;
+  int loss_blocks, child_blocks, parent_blocks, grad_rows;   // grad_rows: rows of a wgrad block
 };
 TdesPlan tdes_plan(const graft_tdes_dims &d, int G, int P);
 struct TdesWorkspace {   // element counts of the trainer's buffers
-  int64_t dyc, dyp, part_u, part_d, part_w;
+  int64_t dyc, dyp, wsum, part_u, part_d, part_w;
 };
 TdesWorkspace tdes_workspace(const graft_tdes_dims &d);
 bool tdes_shape_supported(int E, int m, int L, int K);

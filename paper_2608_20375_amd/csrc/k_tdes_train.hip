@@ -11,16 +11,27 @@
 //   dL/dg_parent = sum over parent rows of e (dL/da)^T,
 //   dL/dg_child  = sum over child rows of e (dL/db)^T.
 //
+// A group's children share the parent: dL/db_r = sk delta_r abar, so its part of
+// dL/dg_child is the outer product of sum_r sk delta_r e_r (formed from the
+// embedding rows the wave still holds) and abar: one row a group for the
+// contraction instead of K.
+//
 // loss_kernel (one wave per group or tile of 8 pairs): gathers the item's
-//   embedding rows (16-byte loads), projects them on MFMA
-//   (v_mfma_f32_16x16x4_f32, 16 rows x 16 score dimensions per instruction;
-//   g_parent and g_child staged in LDS), forms f, the objectives and dL/df,
-//   and writes dL/da, dL/db of every row (fp32, m padded to a multiple of 16)
-//   plus per-block sums of the depth-embedding and scale gradients and of the
-//   objectives.  Few registers per wave: many waves in flight hide the gathers.
-// wgrad_kernel: the two contractions on MFMA, 4 rows per instruction, over
-//   contiguous row chunks (the embedding rows come back from L2 / MALL, 16
-//   bytes per lane); per-block partial gradients.
+//   embedding rows (16-byte loads; the item's ids one item ahead), projects them
+//   on MFMA (v_mfma_f32_16x16x4_f32, 16 rows x 16 score dimensions per
+//   instruction; g_parent and g_child staged in LDS), forms f, the objectives and
+//   dL/df, and writes a group's weighted child sum, abar and dL/da, a pair's dL/da
+//   and dL/db (fp32, m padded to a multiple of 16), plus per-block sums of the
+//   depth-embedding and scale gradients and of the objectives.  With up to 16
+//   children every row of 16 lanes holds all of them, so no softmax sum crosses
+//   the rows.  Latency-bound (gathers, then a chain of sums): three blocks a CU
+//   and two items a wave.
+// wgrad_kernel: the two contractions on MFMA, 4 rows per instruction; a wave owns
+//   a tile of the gradient and goes through all rows of its block, 12 steps'
+//   loads at a time, so nothing is summed across waves; per-block partials.
+// G = P = 4096, E = 128, m = 32, K = 16 (us): loss 28.6 -> 25.9, wgrad 22.0 (K rows
+//   a group, a tile of rows a wave, waves summed through LDS) -> 9.9, step 52.4 ->
+//   38.6; G = P = 512, E = 64, m = 16, K = 8: wgrad 8.6 -> 4.4, step 23.3 -> 18.9.
 // update_kernel: sums every partial in fp64 in a fixed order (a step is
 //   deterministic), then applies AdamW to every parameter.
 #include <cmath>
@@ -34,8 +45,9 @@ constexpr int kLossWaves = 4;
 constexpr int kLossThreads = kLossWaves * kWave;
 constexpr int kGradWaves = 8;
 constexpr int kGradThreads = kGradWaves * kWave;
-constexpr int kGradRowsPerWave = 32;
-constexpr int kGradRows = kGradWaves * kGradRowsPerWave;   // rows per wgrad block
+constexpr int kGradTarget = 256;      // wgrad blocks: one a CU
+constexpr int kGradBatch = 12;        // 4-row steps loaded together
+constexpr int kMinGradRows = 16;      // rows a wgrad block takes at the least
 constexpr int kMaxEM = 4096;          // E * M16, M16 = m rounded up to 16
 constexpr int kMaxLM = 1024;          // L * M16
 
@@ -49,8 +61,9 @@ struct TrainArgs {
   const int32_t *parent, *depth, *child, *target, *pairs;
   const float *logq, *z;
   float c_kl, c_bce, c_pair, gamma, w1;
-  float *dyc;            // [G*K + 2P, M16] dL/db of the child-tower rows
+  float *dyc;            // [G + 2P, M16] dL/db of the child-tower rows (abar for a group)
   float *dyp;            // [G + 2P, M16] dL/da of the parent-tower rows
+  float *wsum;           // [G, E] a group's child rows weighted by sk delta
   float *part_u;         // L*m per loss block (chunked)
   double *part_d;        // [loss blocks, 4]: ds, sum KL, sum pair, sum BCE
   float *part_w;         // E*m per child-side then parent-side wgrad block (chunked)
@@ -129,20 +142,36 @@ __device__ __forceinline__ void load16(const float *row, bool valid, float4 (&ev
   for (int kb = 0; kb < EB; ++kb)
     ev[kb] = valid ? ld4(row + kb * 16 + 4 * q) : make_float4(0.0f, 0.0f, 0.0f, 0.0f);
 }
+// The projection's values are read one block of 16 entries ahead, and the
+// scheduler is held to that: it would otherwise read them all first, and their
+// registers would cost the third block of a CU.
 template <int NT, int EB>
 __device__ __forceinline__ void mma16(const float4 (&ev)[EB], const float *gs, v4f (&y)[NT]) {
   constexpr int SG = NT * 16 + 4;
   const int lane = lane_id(), q = lane >> 4, c16 = lane & 15;
 #pragma unroll
   for (int nt = 0; nt < NT; ++nt) y[nt] = v4f{0.0f, 0.0f, 0.0f, 0.0f};
+  const float *gb = gs + 4 * q * SG + c16;
+  float g[2][4][NT];
+#pragma unroll
+  for (int j = 0; j < 4; ++j)
+#pragma unroll
+    for (int nt = 0; nt < NT; ++nt) g[0][j][nt] = gb[j * SG + nt * 16];
 #pragma unroll
   for (int kb = 0; kb < EB; ++kb) {
-    const float *gb = gs + (kb * 16 + 4 * q) * SG + c16;
+    if (kb + 1 < EB) {
+#pragma unroll
+      for (int j = 0; j < 4; ++j)
+#pragma unroll
+        for (int nt = 0; nt < NT; ++nt)
+          g[(kb + 1) & 1][j][nt] = gb[((kb + 1) * 16 + j) * SG + nt * 16];
+    }
     const float e4[4] = {ev[kb].x, ev[kb].y, ev[kb].z, ev[kb].w};
 #pragma unroll
     for (int j = 0; j < 4; ++j)
 #pragma unroll
-      for (int nt = 0; nt < NT; ++nt) y[nt] = mfma(e4[j], gb[j * SG + nt * 16], y[nt]);
+      for (int nt = 0; nt < NT; ++nt) y[nt] = mfma(e4[j], g[kb & 1][j][nt], y[nt]);
+    __builtin_amdgcn_sched_barrier(0);
   }
 }
 template <int NT, int EB>
@@ -172,27 +201,107 @@ __device__ __forceinline__ LossLds loss_lds(char *base, int E, int M16, int L) {
   return s;
 }
 
+// What an item reads before its embedding rows, loaded one item ahead: a group's
+// parent, depth, target and (per lane) child, log q and target logit, or a pair
+// edge's parent, child and depth.
+struct ItemIn {
+  int p, c, d, tgt;
+  float lq, zt;
+};
+
+// The child row of a group that a lane owns for the softmaxes: with one tile of
+// children every row of 16 lanes holds all of them, so no sum crosses the rows.
+template <int RT>
+__device__ __forceinline__ int own_row() {
+  return RT == 1 ? lane_id() & 15 : lane_id();
+}
+template <int RT>
+__device__ __forceinline__ float rows_sum(float v) {
+  return RT == 1 ? sum16(v) : wave_sum(v);
+}
+template <int RT>
+__device__ __forceinline__ float rows_max(float v) {
+  if (RT != 1) return wave_max(v);
+  v = fmaxf(v, xorf(v, 1));
+  v = fmaxf(v, xorf(v, 2));
+  v = fmaxf(v, xorf(v, 4));
+  return fmaxf(v, xorf(v, 8));
+}
+
+template <int RT>
+__device__ __forceinline__ ItemIn load_item(const TrainArgs &a, int it, int items) {
+  ItemIn x{0, 0, 1, -1, 0.0f, -INFINITY};
+  if (it >= items) return x;
+  if (it < a.G) {
+    const int r = own_row<RT>();
+    x.p = a.parent[it];
+    x.d = a.depth[it];
+    x.tgt = a.target[it];
+    if (r < a.K) {
+      const int64_t i = static_cast<int64_t>(it) * a.K + r;
+      x.c = a.child[i];
+      x.lq = a.logq[i];
+      x.zt = a.z[i];
+    }
+  } else {
+    // edge r = c16 of the tile: pair tile*8 + r/2, v+ for even r, v- for odd
+    const int c16 = lane_id() & 15, pr = (it - a.G) * 8 + (c16 >> 1);
+    if (pr < a.P) {
+      const int32_t *pe = a.pairs + static_cast<int64_t>(pr) * 6 + 3 * (c16 & 1);
+      x.p = pe[0];
+      x.c = pe[1];
+      x.d = pe[2];
+    }
+  }
+  return x;
+}
+
+// Sum of v[0, N) over each row of 16 lanes, scattered: halves are exchanged
+// while there is more than one value, so the steps cost N / 2 + N / 4 + ...
+// adds instead of 4 N.  Afterwards v[0] (and v[1] with N = 32) of lane c16 is the
+// sum of value c16 N / 16 on.
+template <int n, int STEP, int N>
+__device__ __forceinline__ void scatter_step(float (&v)[N]) {
+  if constexpr (n > 1) {
+    const bool up = (lane_id() & STEP) != 0;
+#pragma unroll
+    for (int i = 0; i < n / 2; ++i) {
+      const float keep = up ? v[n / 2 + i] : v[i], give = up ? v[i] : v[n / 2 + i];
+      v[i] = keep + xorf(give, STEP);
+    }
+  } else {
+    v[0] += xorf(v[0], STEP);
+  }
+}
+template <int N>
+__device__ __forceinline__ void scatter_sum16(float (&v)[N]) {
+  constexpr int n4 = N > 1 ? N / 2 : 1, n2 = n4 > 1 ? n4 / 2 : 1, n1 = n2 > 1 ? n2 / 2 : 1;
+  scatter_step<N, 8>(v);
+  scatter_step<n4, 4>(v);
+  scatter_step<n2, 2>(v);
+  scatter_step<n1, 1>(v);
+}
+
 template <int NT, int EB, int RT>
 __device__ __forceinline__ void group_item(const TrainArgs &a, const LossLds &s, int wave, int g,
-                                           float sk, float inv_sqrt_m, double (&tot)[4]) {
+                                           const ItemIn &in, float sk, float inv_sqrt_m,
+                                           double (&tot)[4]) {
   constexpr int E = EB * 16, M16 = NT * 16;
   const int lane = lane_id(), q = lane >> 4, c16 = lane & 15;
   const int K = a.K;
-  const int64_t gk = static_cast<int64_t>(g) * K;
-  const int p = a.parent[g], d = a.depth[g];
-  // lane r < K owns child row r for the softmaxes; its inputs load early
-  const bool own = lane < K;
-  const int ctok = own ? a.child[gk + lane] : 0;
-  const float lq = own ? a.logq[gk + lane] : 0.0f;
-  const float zt = own ? a.z[gk + lane] : -INFINITY;
-  const int tgt = a.target[g];
-  float *dyc = a.dyc + gk * M16;
+  const int p = in.p, d = in.d;
+  const int own_r = own_row<RT>();
+  const bool own = own_r < K;
+  const int ctok = in.c;
+  const float lq = in.lq, zt = in.zt;
+  float *dyc = a.dyc + static_cast<int64_t>(g) * M16;
   float *dyp = a.dyp + static_cast<int64_t>(g) * M16;
+  float *wsum = a.wsum + static_cast<int64_t>(g) * E;
   const bool bad = p < 0 || p >= a.V || d < 1 || d > a.L || (own && (ctok < 0 || ctok >= a.V));
   if (__any(bad)) {
     // dropped: zero rows keep the contractions exact for the rest
-    for (int i = lane; i < K * M16; i += kWave) dyc[i] = 0.0f;
-    if (lane < M16) dyp[lane] = 0.0f;
+    for (int i = lane; i < E; i += kWave) wsum[i] = 0.0f;
+    if (lane < M16) dyc[lane] = dyp[lane] = 0.0f;
     if (lane == 0) atomicOr(a.error_flag, 1u);
     return;
   }
@@ -207,21 +316,26 @@ __device__ __forceinline__ void group_item(const TrainArgs &a, const LossLds &s,
   {
     float4 evp[EB];
     load16<EB>(a.emb + static_cast<int64_t>(p) * E, true, evp);
-    load16<EB>(a.emb + static_cast<int64_t>(__shfl(ctok, c16)) * E, c16 < K, evc0);
+    const int tok0 = RT == 1 ? ctok : __shfl(ctok, c16);
+    load16<EB>(a.emb + static_cast<int64_t>(tok0) * E, c16 < K, evc0);
     constexpr int SG = M16 + 4;
+    float acc0[NT];
 #pragma unroll
-    for (int nt = 0; nt < NT; ++nt) {
-      float acc0 = 0.0f;
+    for (int nt = 0; nt < NT; ++nt) acc0[nt] = 0.0f;
 #pragma unroll
-      for (int kb = 0; kb < EB; ++kb) {
+    for (int kb = 0; kb < EB; ++kb) {
+#pragma unroll
+      for (int nt = 0; nt < NT; ++nt) {
         const float *gcol = s.gs0 + (kb * 16 + 4 * q) * SG + nt * 16 + c16;
-        acc0 = fmaf(evp[kb].x, gcol[0], acc0);
-        acc0 = fmaf(evp[kb].y, gcol[SG], acc0);
-        acc0 = fmaf(evp[kb].z, gcol[2 * SG], acc0);
-        acc0 = fmaf(evp[kb].w, gcol[3 * SG], acc0);
+        acc0[nt] = fmaf(evp[kb].x, gcol[0], acc0[nt]);
+        acc0[nt] = fmaf(evp[kb].y, gcol[SG], acc0[nt]);
+        acc0[nt] = fmaf(evp[kb].z, gcol[2 * SG], acc0[nt]);
+        acc0[nt] = fmaf(evp[kb].w, gcol[3 * SG], acc0[nt]);
       }
-      abar[nt] = sum_rows(acc0) + us[nt * 16 + c16];
+      if (kb & 1) __builtin_amdgcn_sched_barrier(0);
     }
+#pragma unroll
+    for (int nt = 0; nt < NT; ++nt) abar[nt] = sum_rows(acc0[nt]) + us[nt * 16 + c16];
   }
 
   // child tower, RT tiles of 16 rows (kept for dL/da)
@@ -258,33 +372,58 @@ __device__ __forceinline__ void group_item(const TrainArgs &a, const LossLds &s,
   wave_lds_sync();
 
   // softmaxes over the K children, one row per lane
-  const float f = own ? fs[lane] : 0.0f;
+  const float f = own ? fs[own_r] : 0.0f;
   const float x = own ? lq + f : -INFINITY;
-  const float y = own && ctok == tgt ? 1.0f : 0.0f;
-  const float mx = wave_max(x), mz = wave_max(zt);
-  const float lse_x = mx + logf(wave_sum(own ? expf(x - mx) : 0.0f));
-  const float lse_z = mz + logf(wave_sum(own ? expf(zt - mz) : 0.0f));
-  float dl = 0.0f, kl = 0.0f, bce = 0.0f;
+  const float y = own && ctok == in.tgt ? 1.0f : 0.0f;
+  const float mx = rows_max<RT>(x), mz = rows_max<RT>(zt);
+  const float lse_x = mx + logf(rows_sum<RT>(own ? expf(x - mx) : 0.0f));
+  const float lse_z = mz + logf(rows_sum<RT>(own ? expf(zt - mz) : 0.0f));
+  float dl = 0.0f;
   if (own) {
     const float lpt = zt - lse_z, lpth = x - lse_x;
     const float pt = expf(lpt), pth = expf(lpth);
     const float dbce = -a.w1 * y * sigmoid(-f) + (1.0f - y) * sigmoid(f);
     dl = a.c_kl * (pth - pt) + a.c_bce * dbce;
-    kl = pt * (lpt - lpth);
-    bce = a.w1 * y * softplus(-f) + (1.0f - y) * softplus(f);
+    if (RT != 1 || q == 0) {   // each row once; the lanes add up at the end
+      tot[0] += static_cast<double>(dl * dots[own_r]);
+      tot[1] += static_cast<double>(pt * (lpt - lpth));
+      tot[3] += static_cast<double>(a.w1 * y * softplus(-f) + (1.0f - y) * softplus(f));
+    }
   }
-  delta[lane] = dl;
-  const float sd = wave_sum(dl);
-  tot[0] += static_cast<double>(wave_sum(own ? dl * dots[lane] : 0.0f));
-  tot[1] += static_cast<double>(wave_sum(kl));
-  tot[3] += static_cast<double>(wave_sum(bce));
+  delta[own_r] = dl;
+  const float sd = rows_sum<RT>(dl);
   wave_lds_sync();
 
-  // dL/db_r = sk delta_r abar (lanes of row q of lanes take rows q, q + 4, ...)
-  for (int r = q; r < K; r += 4) {
-    const float c = sk * delta[r];
+  // dL/db_r = sk delta_r abar for every child, so the group's part of dL/dg_child
+  // is the outer product of sum_r sk delta_r e_r and abar: one row a group for
+  // the contraction instead of K
+  {
+    float v[4 * EB];
 #pragma unroll
-    for (int nt = 0; nt < NT; ++nt) dyc[r * M16 + nt * 16 + c16] = c * abar[nt];
+    for (int rt = 0; rt < RT; ++rt) {
+      if (rt * 16 >= K) continue;
+      const int row = rt * 16 + c16;
+      float4 ev[EB];
+      if (rt > 0)
+        load16<EB>(a.emb + static_cast<int64_t>(__shfl(ctok, row)) * E, row < K, ev);
+      const float c = sk * (RT == 1 ? dl : row < K ? delta[row] : 0.0f);
+#pragma unroll
+      for (int kb = 0; kb < EB; ++kb) {
+        const float4 e = rt == 0 ? evc0[kb] : ev[kb];
+        v[4 * kb + 0] = rt == 0 ? c * e.x : fmaf(c, e.x, v[4 * kb + 0]);
+        v[4 * kb + 1] = rt == 0 ? c * e.y : fmaf(c, e.y, v[4 * kb + 1]);
+        v[4 * kb + 2] = rt == 0 ? c * e.z : fmaf(c, e.z, v[4 * kb + 2]);
+        v[4 * kb + 3] = rt == 0 ? c * e.w : fmaf(c, e.w, v[4 * kb + 3]);
+      }
+    }
+    scatter_sum16<4 * EB>(v);
+    // value i is entry (i / 4) * 16 + 4 q + i % 4
+    const int i0 = c16 * 4 * EB / 16, k = (i0 >> 2) * 16 + 4 * q + (i0 & 3);
+    if constexpr (EB == 8) {
+      *reinterpret_cast<float2 *>(wsum + k) = make_float2(v[0], v[1]);
+    } else if (EB == 4 || (c16 & 1) == 0) {
+      wsum[k] = v[0];
+    }
   }
   // dL/da = sk sum_r delta_r bbar_r; the depth embedding gets dL/da + sum_r dL/db_r
 #pragma unroll
@@ -300,6 +439,7 @@ __device__ __forceinline__ void group_item(const TrainArgs &a, const LossLds &s,
     const float dA = sk * sum_rows(part);
     if (q == 0) {
       dyp[nt * 16 + c16] = dA;
+      dyc[nt * 16 + c16] = abar[nt];
       s.du[(wave * a.L + d - 1) * M16 + nt * 16 + c16] += dA + sk * abar[nt] * sd;
     }
   }
@@ -308,16 +448,15 @@ __device__ __forceinline__ void group_item(const TrainArgs &a, const LossLds &s,
 
 template <int NT, int EB>
 __device__ __forceinline__ void pair_item(const TrainArgs &a, const LossLds &s, int wave, int tile,
-                                          float sk, float inv_sqrt_m, double (&tot)[4]) {
+                                          const ItemIn &in, float sk, float inv_sqrt_m,
+                                          double (&tot)[4]) {
   constexpr int E = EB * 16, M16 = NT * 16;
   const int lane = lane_id(), q = lane >> 4, c16 = lane & 15;
   // edge r = c16 of the tile: pair tile*8 + r/2, v+ for even r, v- for odd
-  const int pr = tile * 8 + (c16 >> 1);
-  const bool exists = pr < a.P;
-  const int32_t *pe = a.pairs + static_cast<int64_t>(exists ? pr : 0) * 6 + 3 * (c16 & 1);
-  const int ptk = exists ? pe[0] : 0, ctk = exists ? pe[1] : 0, dd = exists ? pe[2] : 1;
-  const int64_t pbase = a.G + static_cast<int64_t>(tile) * 16;   // dyp row of edge 0
-  const int64_t cbase = static_cast<int64_t>(a.G) * a.K + static_cast<int64_t>(tile) * 16;
+  const bool exists = tile * 8 + (c16 >> 1) < a.P;
+  const int ptk = in.p, ctk = in.c, dd = in.d;
+  const int64_t pbase = a.G + static_cast<int64_t>(tile) * 16;   // dyp and dyc row of edge 0
+  const int64_t cbase = pbase;
   const bool bad_row = exists && (ptk < 0 || ptk >= a.V || ctk < 0 || ctk >= a.V || dd < 1 || dd > a.L);
   if (__any(bad_row)) {
     for (int i = lane; i < 16 * M16; i += kWave) {
@@ -366,9 +505,10 @@ __device__ __forceinline__ void pair_item(const TrainArgs &a, const LossLds &s, 
     dl[2 * h + 1] = t;
     dsum += -t * dot[2 * h] + t * dot[2 * h + 1];
   }
-  // each lane holds its row of lanes' two pairs: the 4 rows of lanes sum to the tile
-  tot[0] += static_cast<double>(sum_rows(dsum));
-  tot[2] += static_cast<double>(sum_rows(loss));
+  if (c16 == 0) {   // each row of lanes holds its two pairs; the lanes add up at the end
+    tot[0] += static_cast<double>(dsum);
+    tot[2] += static_cast<double>(loss);
+  }
   // dL/da = sk delta bbar, dL/db = sk delta abar; the depth embedding gets both
   // (LDS adds: rows of one instruction may share a depth)
 #pragma unroll
@@ -388,39 +528,36 @@ __device__ __forceinline__ void pair_item(const TrainArgs &a, const LossLds &s, 
 }
 
 template <int NT, int EB, int RT>
-__global__ void __launch_bounds__(kLossThreads)
+__global__ void __launch_bounds__(kLossThreads, RT == 1 ? 3 : 2)
 loss_kernel(TrainArgs a) {
   constexpr int E = EB * 16, M16 = NT * 16, SG = M16 + 4;
   extern __shared__ __align__(16) char lds_raw[];
   const LossLds s = loss_lds(lds_raw, E, M16, a.L);
   const int tid = threadIdx.x, lane = lane_id(), wave = tid / kWave;
   const int m = a.m, L = a.L;
-  // stage g_parent, g_child as [E][SG] (columns m.. zero): with m a multiple
-  // of 4 every thread's float4 loads go out together
-  if (m % 4 == 0) {
-    const int n4 = E * m / 4;
-    for (int i = tid; i < E * SG; i += kLossThreads) {
-      const int n = i % SG;
-      if (n >= m) s.gs0[i] = s.gs1[i] = 0.0f;
-    }
-    constexpr int kPer = (E * M16 / 4 + kLossThreads - 1) / kLossThreads;
+  // the first item's inputs are in flight while the projections are staged
+  const int items = a.G + (a.P + 7) / 8;
+  const int W = gridDim.x * kLossWaves;
+  int it = blockIdx.x * kLossWaves + wave;
+  ItemIn in = load_item<RT>(a, it, items);
+  // stage g_parent, g_child as [E][SG] (columns m.. zero); every thread's loads
+  // go out together when m fills its tiles (the 4 columns past M16 are padding)
+  if (m == M16) {
+    constexpr int n4 = E * M16 / 4, kPer = (n4 + kLossThreads - 1) / kLossThreads;
     float4 v0[kPer], v1[kPer];
 #pragma unroll
     for (int j = 0; j < kPer; ++j) {
-      const int v = tid + j * kLossThreads;
-      if (v < n4) {
-        v0[j] = ld4(a.theta + 4 * v);
-        v1[j] = ld4(a.theta + E * m + 4 * v);
-      }
+      const int v = tid + j * kLossThreads < n4 ? tid + j * kLossThreads : 0;
+      v0[j] = ld4(a.theta + 4 * v);
+      v1[j] = ld4(a.theta + E * M16 + 4 * v);
     }
 #pragma unroll
     for (int j = 0; j < kPer; ++j) {
       const int v = tid + j * kLossThreads;
       if (v < n4) {
-        const int k = 4 * v / m, n = 4 * v % m;
-        float *d0 = s.gs0 + k * SG + n, *d1 = s.gs1 + k * SG + n;
-        d0[0] = v0[j].x, d0[1] = v0[j].y, d0[2] = v0[j].z, d0[3] = v0[j].w;
-        d1[0] = v1[j].x, d1[1] = v1[j].y, d1[2] = v1[j].z, d1[3] = v1[j].w;
+        const int to = 4 * v / M16 * SG + 4 * v % M16;
+        *reinterpret_cast<float4 *>(s.gs0 + to) = v0[j];
+        *reinterpret_cast<float4 *>(s.gs1 + to) = v1[j];
       }
     }
   } else {
@@ -440,19 +577,20 @@ loss_kernel(TrainArgs a) {
   const float sk = a.theta[2 * E * m + L * m] * inv_sqrt_m;
   __syncthreads();
 
-  double tot[4] = {0.0, 0.0, 0.0, 0.0};
-  const int T = (a.P + 7) / 8;
-  const int items = a.G + T;
-  const int W = gridDim.x * kLossWaves;
-  for (int it = blockIdx.x * kLossWaves + wave; it < items; it += W) {
+  double tot[4] = {0.0, 0.0, 0.0, 0.0};   // per lane
+  for (; it < items; it += W) {
+    const ItemIn next = load_item<RT>(a, it + W, items);
     if (it < a.G)
-      group_item<NT, EB, RT>(a, s, wave, it, sk, inv_sqrt_m, tot);
+      group_item<NT, EB, RT>(a, s, wave, it, in, sk, inv_sqrt_m, tot);
     else
-      pair_item<NT, EB>(a, s, wave, it - a.G, sk, inv_sqrt_m, tot);
+      pair_item<NT, EB>(a, s, wave, it - a.G, in, sk, inv_sqrt_m, tot);
+    in = next;
   }
-  if (lane == 0) {
 #pragma unroll
-    for (int j = 0; j < 4; ++j) s.wd[wave * 4 + j] = tot[j];
+  for (int j = 0; j < 4; ++j) {
+#pragma unroll
+    for (int o = 1; o < kWave; o <<= 1) tot[j] += xor_lane_f64(tot[j], o);
+    if (lane == 0) s.wd[wave * 4 + j] = tot[j];
   }
   __syncthreads();
   for (int i = tid; i < L * m; i += kLossThreads) {
@@ -468,90 +606,102 @@ loss_kernel(TrainArgs a) {
   }
 }
 
-// Token of row `row` of one side: child side = the children of the groups,
-// then the child of every pair edge; parent side = the parents of the groups,
-// then the parent of every pair edge (edge 2i is v+ of pair i, 2i + 1 its v-).
-__device__ __forceinline__ int row_token(const TrainArgs &a, int side, int64_t row) {
-  const int64_t first = side == 0 ? static_cast<int64_t>(a.G) * a.K : a.G;
-  if (row < first) return side == 0 ? a.child[row] : a.parent[row];
-  const int64_t e = row - first;
-  return a.pairs[(e >> 1) * 6 + 3 * (e & 1) + (side == 0 ? 1 : 0)];
-}
-
 // dL/dg = sum over the rows of one side of e_row (dL/dy_row)^T, 4 rows per
-// instruction.  Lane (q, c16) loads 16 bytes of embedding row 4s + q,
-// entries 64h + 4 c16 + j, so tile (nt, 4h + j) of the transposed gradient
-// holds n = nt*16 + 4q + i (component i), k = 64h + 4 c16 + j.
+// instruction.  The rows: on the child side a group's weighted child sum and
+// abar, on the parent side the group's parent and dL/da, then on both the edges
+// of the pairs (edge 2i is v+ of pair i, 2i + 1 its v-).  Wave w owns the k tile
+// w % EB of the transposed gradient and every row group w / EB of its block, so
+// that no accumulator is summed across waves that share a tile unless EB < 8
+// (then kGradWaves / EB of them, in order).  Lane (q, c16) loads entry
+// kt*16 + c16 of embedding row 4s + q (64-byte runs) and component i of its tile
+// nt holds n = nt*16 + 4q + i, k = kt*16 + c16.
 template <int NT, int EB>
 __global__ void __launch_bounds__(kGradThreads)
-wgrad_kernel(TrainArgs a, int child_blocks) {
-  constexpr int E = EB * 16, M16 = NT * 16, KH = (E + 63) / 64;
-  __shared__ float red[kMaxEM];
-  const int tid = threadIdx.x, lane = lane_id(), wave = tid / kWave;
+wgrad_kernel(TrainArgs a, int child_blocks, int block_rows) {
+  constexpr int E = EB * 16, M16 = NT * 16, RG = kGradWaves / EB;
+  __shared__ float red[RG > 1 ? RG * E * M16 : 1];
+  __shared__ int s_tok[kGradThreads];
+  const int tid = threadIdx.x, lane = lane_id();
+  const int wave = __builtin_amdgcn_readfirstlane(tid / kWave);
   const int q = lane >> 4, c16 = lane & 15;
   const int side = blockIdx.x < child_blocks ? 0 : 1;
   const int blk = side == 0 ? blockIdx.x : blockIdx.x - child_blocks;
-  const int64_t rows = side == 0 ? static_cast<int64_t>(a.G) * a.K + 2 * static_cast<int64_t>(a.P)
-                                 : static_cast<int64_t>(a.G) + 2 * static_cast<int64_t>(a.P);
+  const int64_t rows = a.G + 2 * static_cast<int64_t>(a.P);
   const float *dy = side == 0 ? a.dyc : a.dyp;
-  v4f acc[NT][4 * KH];
+  const int kt = wave % EB, rg = wave / EB;
+  v4f acc[NT];
 #pragma unroll
-  for (int nt = 0; nt < NT; ++nt)
-#pragma unroll
-    for (int t = 0; t < 4 * KH; ++t) acc[nt][t] = v4f{0.0f, 0.0f, 0.0f, 0.0f};
-  const int64_t r0 = static_cast<int64_t>(blk) * kGradRows + wave * kGradRowsPerWave;
-  // the tokens of the wave's rows, one per lane, in one round trip
-  int mytok = -1;
-  if (lane < kGradRowsPerWave && r0 + lane < rows) mytok = row_token(a, side, r0 + lane);
-  const bool kin = 4 * c16 < E;   // E = 32 uses half the lanes of a 64-entry block
-#pragma unroll 4
-  for (int st = 0; st < kGradRowsPerWave; st += 4) {
-    const int64_t r = r0 + st + q;
-    const int tok = __shfl(mytok, st + q);
-    const bool live = r < rows && tok >= 0 && tok < a.V;
-    const float *er = a.emb + static_cast<int64_t>(live ? tok : 0) * E + 4 * c16;
-    const float *yr = dy + (live ? r : 0) * M16 + c16;
-    float av[NT];
-    float4 ev[KH];
-#pragma unroll
-    for (int nt = 0; nt < NT; ++nt) av[nt] = live ? yr[nt * 16] : 0.0f;
-#pragma unroll
-    for (int h = 0; h < KH; ++h)
-      ev[h] = live && kin ? ld4(er + 64 * h) : make_float4(0.0f, 0.0f, 0.0f, 0.0f);
-#pragma unroll
-    for (int nt = 0; nt < NT; ++nt)
-#pragma unroll
-      for (int h = 0; h < KH; ++h) {
-        acc[nt][4 * h + 0] = mfma(av[nt], ev[h].x, acc[nt][4 * h + 0]);
-        acc[nt][4 * h + 1] = mfma(av[nt], ev[h].y, acc[nt][4 * h + 1]);
-        acc[nt][4 * h + 2] = mfma(av[nt], ev[h].z, acc[nt][4 * h + 2]);
-        acc[nt][4 * h + 3] = mfma(av[nt], ev[h].w, acc[nt][4 * h + 3]);
+  for (int nt = 0; nt < NT; ++nt) acc[nt] = v4f{0.0f, 0.0f, 0.0f, 0.0f};
+  const int64_t first = static_cast<int64_t>(blk) * block_rows;
+  const int64_t last = first + block_rows < rows ? first + block_rows : rows;
+  for (int64_t r0 = first; r0 < last; r0 += kGradThreads) {
+    // the tokens of up to kGradThreads rows in one round trip; -1: no row, -2: a
+    // group's own sum
+    const int64_t r = r0 + tid;
+    int tok = -1;
+    if (r < last) {
+      if (r >= a.G) {
+        const int64_t e = r - a.G;
+        tok = a.pairs[(e >> 1) * 6 + 3 * (e & 1) + (side == 0 ? 1 : 0)];
+      } else {
+        tok = side == 0 ? -2 : a.parent[r];
       }
-  }
-  // block sum in wave order into red[n][k] (one wave at a time measured faster
-  // than four LDS slots added pairwise)
-  for (int wv = 0; wv < kGradWaves; ++wv) {
-    if (wave == wv && kin) {
-#pragma unroll
-      for (int nt = 0; nt < NT; ++nt)
-#pragma unroll
-        for (int t = 0; t < 4 * KH; ++t)
-#pragma unroll
-          for (int i = 0; i < 4; ++i) {
-            const int k = 64 * (t / 4) + 4 * c16 + (t % 4);
-            const int idx = (nt * 16 + 4 * q + i) * E + k;
-            if (k < E) red[idx] = (wv ? red[idx] : 0.0f) + acc[nt][t][i];
-          }
+      if (tok != -2 && (tok < 0 || tok >= a.V)) tok = -1;
     }
+    if (r0 != first) __syncthreads();
+    s_tok[tid] = tok;
     __syncthreads();
+    const int n = last - r0 < kGradThreads ? static_cast<int>(last - r0) : kGradThreads;
+    // kGradBatch steps at a time, every load issued before the first product
+    for (int s0 = 4 * rg; s0 < n; s0 += 4 * RG * kGradBatch) {
+      float ev[kGradBatch], av[kGradBatch][NT];
+#pragma unroll
+      for (int j = 0; j < kGradBatch; ++j) {
+        if (s0 + 4 * RG * j >= n) break;   // uniform in the wave
+        const int st = s0 + 4 * RG * j + q;
+        const int tk = s_tok[st < kGradThreads ? st : 0];
+        const bool live = st < n && tk != -1;
+        const int64_t row = live ? r0 + st : 0;
+        const float *er = live && tk == -2 ? a.wsum + row * E
+                                           : a.emb + static_cast<int64_t>(live ? tk : 0) * E;
+        const float *yr = dy + row * M16 + c16;
+        ev[j] = live ? er[kt * 16 + c16] : 0.0f;
+#pragma unroll
+        for (int nt = 0; nt < NT; ++nt) av[j][nt] = live ? yr[nt * 16] : 0.0f;
+      }
+#pragma unroll
+      for (int j = 0; j < kGradBatch; ++j) {
+        if (s0 + 4 * RG * j >= n) break;
+#pragma unroll
+        for (int nt = 0; nt < NT; ++nt) acc[nt] = mfma(av[j][nt], ev[j], acc[nt]);
+      }
+    }
   }
   const int m = a.m, em = E * m;
   const int nb = side == 0 ? child_blocks : gridDim.x - child_blocks;
   float *out = a.part_w + (side == 0 ? 0 : chunked_size(em, child_blocks));
-  for (int i = tid; i < em; i += kGradThreads) {
-    const int idx = (i % m) * E + i / m;
-    const float v = red[idx];
-    out[chunked(i, nb, blk)] = v;
+  if constexpr (RG == 1) {
+#pragma unroll
+    for (int nt = 0; nt < NT; ++nt)
+#pragma unroll
+      for (int i = 0; i < 4; ++i) {
+        const int c = nt * 16 + 4 * q + i;
+        if (c < m) out[chunked((kt * 16 + c16) * m + c, nb, blk)] = acc[nt][i];
+      }
+  } else {
+#pragma unroll
+    for (int nt = 0; nt < NT; ++nt)
+#pragma unroll
+      for (int i = 0; i < 4; ++i)
+        red[(rg * E + kt * 16 + c16) * M16 + nt * 16 + 4 * q + i] = acc[nt][i];
+    __syncthreads();
+    for (int i = tid; i < em; i += kGradThreads) {
+      const int at = i / m * M16 + i % m;
+      float v = red[at];
+#pragma unroll
+      for (int g = 1; g < RG; ++g) v += red[g * E * M16 + at];
+      out[chunked(i, nb, blk)] = v;
+    }
   }
 }
 
@@ -648,7 +798,7 @@ size_t loss_lds_bytes(int E, int M16, int L) {
 
 template <int NT, int EB>
 bool launch_t(const TrainArgs &a, int nt, int eb, int loss_blocks, int child_blocks,
-              int grad_blocks, hipStream_t stream) {
+              int grad_blocks, int grad_rows, hipStream_t stream) {
   if (nt != NT || eb != EB) return false;
   const size_t lds = loss_lds_bytes(EB * 16, NT * 16, a.L);
   // child tiles of 16 rows per group: K <= 16, 32 or 64
@@ -660,17 +810,17 @@ bool launch_t(const TrainArgs &a, int nt, int eb, int loss_blocks, int child_blo
     hipLaunchKernelGGL((loss_kernel<NT, EB, 4>), dim3(loss_blocks), dim3(kLossThreads), lds, stream, a);
   if (grad_blocks > 0)
     hipLaunchKernelGGL((wgrad_kernel<NT, EB>), dim3(grad_blocks), dim3(kGradThreads), 0, stream, a,
-                       child_blocks);
+                       child_blocks, grad_rows);
   return true;
 }
 
 // the instantiated shapes: E in {32, 64, 128} with E * M16 <= 4096
-bool dispatch(const TrainArgs &a, int nt, int eb, int lb, int cb, int gb, hipStream_t st) {
-  return launch_t<1, 2>(a, nt, eb, lb, cb, gb, st) || launch_t<1, 4>(a, nt, eb, lb, cb, gb, st) ||
-         launch_t<1, 8>(a, nt, eb, lb, cb, gb, st) || launch_t<2, 2>(a, nt, eb, lb, cb, gb, st) ||
-         launch_t<2, 4>(a, nt, eb, lb, cb, gb, st) || launch_t<2, 8>(a, nt, eb, lb, cb, gb, st) ||
-         launch_t<3, 2>(a, nt, eb, lb, cb, gb, st) || launch_t<3, 4>(a, nt, eb, lb, cb, gb, st) ||
-         launch_t<4, 2>(a, nt, eb, lb, cb, gb, st) || launch_t<4, 4>(a, nt, eb, lb, cb, gb, st);
+bool dispatch(const TrainArgs &a, int nt, int eb, int lb, int cb, int gb, int gr, hipStream_t st) {
+  return launch_t<1, 2>(a, nt, eb, lb, cb, gb, gr, st) || launch_t<1, 4>(a, nt, eb, lb, cb, gb, gr, st) ||
+         launch_t<1, 8>(a, nt, eb, lb, cb, gb, gr, st) || launch_t<2, 2>(a, nt, eb, lb, cb, gb, gr, st) ||
+         launch_t<2, 4>(a, nt, eb, lb, cb, gb, gr, st) || launch_t<2, 8>(a, nt, eb, lb, cb, gb, gr, st) ||
+         launch_t<3, 2>(a, nt, eb, lb, cb, gb, gr, st) || launch_t<3, 4>(a, nt, eb, lb, cb, gb, gr, st) ||
+         launch_t<4, 2>(a, nt, eb, lb, cb, gb, gr, st) || launch_t<4, 4>(a, nt, eb, lb, cb, gb, gr, st);
 }
 
 }  // namespace
@@ -679,24 +829,32 @@ TdesPlan tdes_plan(const graft_tdes_dims &d, int G, int P) {
   TdesPlan p;
   const int64_t items = static_cast<int64_t>(G) + (static_cast<int64_t>(P) + 7) / 8;
   const int64_t lb = (items + 2 * kLossWaves - 1) / (2 * kLossWaves);   // about 2 items per wave
-  p.loss_blocks = static_cast<int>(lb < 1 ? 1 : lb > kTdesMaxLossBlocks ? kTdesMaxLossBlocks : lb);
-  const int64_t rc = static_cast<int64_t>(G) * d.top_k + 2 * static_cast<int64_t>(P);
-  const int64_t rp = static_cast<int64_t>(G) + 2 * static_cast<int64_t>(P);
-  p.child_blocks = static_cast<int>((rc + kGradRows - 1) / kGradRows);
-  p.parent_blocks = static_cast<int>((rp + kGradRows - 1) / kGradRows);
+  // at most the blocks that run at once: three a CU with one tile of children, two
+  // with more
+  const int most = d.top_k <= 16 ? 768 : 512;
+  p.loss_blocks = static_cast<int>(lb < 1 ? 1 : lb > most ? most : lb);
+  // as many rows a block as give each CU one
+  const int64_t rows = static_cast<int64_t>(G) + 2 * static_cast<int64_t>(P);   // of each side
+  const int64_t per = ((2 * rows + kGradTarget - 1) / kGradTarget + 3) / 4 * 4;
+  p.grad_rows = static_cast<int>(per < kMinGradRows ? kMinGradRows : per);
+  p.child_blocks = p.parent_blocks = static_cast<int>((rows + p.grad_rows - 1) / p.grad_rows);
   return p;
 }
 
 TdesWorkspace tdes_workspace(const graft_tdes_dims &d) {
-  const TdesPlan most = tdes_plan(d, d.max_groups, d.max_pairs);
   const int64_t m16 = (d.score_dim + 15) / 16 * 16;
+  const int64_t rows = static_cast<int64_t>(d.max_groups) + 2 * static_cast<int64_t>(d.max_pairs);
+  // a side has at most kGradTarget / 2 + 1 blocks, and one per kMinGradRows rows
+  int64_t blocks = (rows + kMinGradRows - 1) / kMinGradRows;
+  if (blocks > kGradTarget / 2 + 1) blocks = kGradTarget / 2 + 1;
   TdesWorkspace w;
-  w.dyc = (static_cast<int64_t>(d.max_groups) * d.top_k + 2 * static_cast<int64_t>(d.max_pairs)) * m16;
-  w.dyp = (static_cast<int64_t>(d.max_groups) + 2 * static_cast<int64_t>(d.max_pairs)) * m16;
-  w.part_u = chunked_size(d.num_pos * d.score_dim, kTdesMaxLossBlocks);
-  w.part_d = 4 * static_cast<int64_t>(kTdesMaxLossBlocks);
-  w.part_w = chunked_size(d.emb_dim * d.score_dim, most.child_blocks) +
-             chunked_size(d.emb_dim * d.score_dim, most.parent_blocks);
+  const int loss = tdes_plan(d, d.max_groups, d.max_pairs).loss_blocks;   // grows with the batch
+  auto whole = [](int64_t n) { return (n + 63) / 64 * 64; };   // parts start on 256-byte boundaries
+  w.dyc = w.dyp = whole(rows * m16);
+  w.wsum = whole(static_cast<int64_t>(d.max_groups) * d.emb_dim);
+  w.part_u = whole(chunked_size(d.num_pos * d.score_dim, loss));
+  w.part_d = 4 * static_cast<int64_t>(loss);
+  w.part_w = 2 * chunked_size(d.emb_dim * d.score_dim, static_cast<int>(blocks));
   return w;
 }
 
@@ -738,12 +896,14 @@ hipError_t launch_tdes_step(graft_tdes *t, const float *emb, const graft_tdes_ba
   a.w1 = h->w1;
   a.dyc = t->dyc;
   a.dyp = t->dyp;
+  a.wsum = t->wsum;
   a.part_u = t->part_u;
   a.part_d = t->part_d;
   a.part_w = t->part_w;
   a.error_flag = t->error_flag;
   const int grad_blocks = plan.child_blocks + plan.parent_blocks;
-  if (!dispatch(a, (m + 15) / 16, E / 16, plan.loss_blocks, plan.child_blocks, grad_blocks, stream))
+  if (!dispatch(a, (m + 15) / 16, E / 16, plan.loss_blocks, plan.child_blocks, grad_blocks, plan.grad_rows,
+                stream))
     return hipErrorInvalidValue;
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) return e;
