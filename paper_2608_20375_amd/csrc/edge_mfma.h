@@ -9,11 +9,10 @@
 //   f = scale * <par[p], chd[c]> / sqrt(m),  S = log q(c) + beta * (f - mean_c f)
 // (the mean over the K children when center != 0), stored at
 // rows[prank[p] * K + col[c]] (selection's token-id order) and, when out is
-// given, at out[p * K + c] (rank order).  Both return this lane's "some stored
-// S > 0"; the whole wave must call them.
-//   edge_tiles (m a multiple of 16): the n_par x K products on fp32 matrix
-//     cores, 16 x 16 tiles of v_mfma_f32_16x16x4f32;
-//   edge_passes (other m): VALU dot products, SEG lanes per parent.
+// given, at out[p * K + c] (rank order).  edge_tiles forms the n_par x K products
+// on fp32 matrix cores, 16 x 16 tiles of v_mfma_f32_16x16x4f32, for m a multiple
+// of 16 (other score dims are padded with zeros), and returns this lane's "some
+// stored S > 0"; the whole wave must call it.
 #pragma once
 
 #include "graft_internal.h"
@@ -151,79 +150,6 @@ __device__ __forceinline__ bool edge_tiles(const EdgeJob (&job)[ND], int ld, int
         }
       }
     }
-  }
-  return pos;
-}
-
-// Sum over each run of seg consecutive lanes (seg a power of two), in every
-// lane of the run: butterfly steps 1, 2, ... seg / 2.
-__device__ __forceinline__ float seg_sum_rt(float v, int seg) {
-#pragma unroll
-  for (int stride = 1; stride < kWave; stride <<= 1)
-    if (stride < seg) v += __uint_as_float(xor_lane(__float_as_uint(v), stride));
-  return v;
-}
-
-// VALU passes: SEG lanes per parent (SEG = K rounded up to a power of two),
-// 64 / SEG parents a pass; lane c of a run keeps child c's row in registers
-// (KQ >= ceil(m / 4) groups of four; with m % 4 != 0 one float at a time)
-// and reads the parent's row from LDS (one address for the whole run).
-template <int KQ>
-__device__ __forceinline__ bool edge_passes(const float *par, const float *chd, int ld, int n_par,
-                                            int K, int m, float fscale, float beta, int center,
-                                            const float *lq, const int32_t *col,
-                                            const int32_t *prank, float *rows, float *out) {
-  const int lane = lane_id();
-  int seg = 1;
-  while (seg < K) seg <<= 1;
-  const int kRows = kWave / seg;
-  const int c = lane & (seg - 1), cc = c < K ? c : 0;
-  const int m4 = (m & 3) == 0 ? m >> 2 : 0;
-  float4 cr[KQ];
-  if (m4 > 0) {
-    const float4 *c4 = reinterpret_cast<const float4 *>(chd + cc * ld);
-#pragma unroll
-    for (int q = 0; q < KQ; ++q) cr[q] = c4[q < m4 ? q : 0];
-#pragma unroll
-    for (int q = 0; q < KQ; ++q)
-      if (q >= m4) cr[q] = make_float4(0.f, 0.f, 0.f, 0.f);
-  }
-  const float lqc = lq[cc];
-  const int colc = col[cc];
-  bool pos = false;
-  for (int p0 = 0; p0 < n_par; p0 += kRows) {
-    const int p = p0 + lane / seg;
-    const bool valid = p < n_par && c < K;
-    const int pp = p < n_par ? p : 0;
-    const int prow = prank ? prank[pp] : 0;
-    const float *pv = par + pp * ld;
-    float a0 = 0.f, a1 = 0.f, a2 = 0.f, a3 = 0.f;
-    if (m4 > 0) {
-      const float4 *p4 = reinterpret_cast<const float4 *>(pv);
-      float4 x[KQ];
-#pragma unroll
-      for (int q = 0; q < KQ; ++q) x[q] = p4[q < m4 ? q : 0];
-#pragma unroll
-      for (int q = 0; q < KQ; ++q) {
-        a0 = __builtin_fmaf(x[q].x, cr[q].x, a0);
-        a1 = __builtin_fmaf(x[q].y, cr[q].y, a1);
-        a2 = __builtin_fmaf(x[q].z, cr[q].z, a2);
-        a3 = __builtin_fmaf(x[q].w, cr[q].w, a3);
-      }
-    } else {
-      const float *cv = chd + cc * ld;
-#pragma unroll 4
-      for (int j = 0; j < m; ++j) a0 = __builtin_fmaf(pv[j], cv[j], a0);
-    }
-    const float f = fscale * ((a0 + a1) + (a2 + a3));
-    float mean = 0.f;
-    if (center) mean = seg_sum_rt(valid ? f : 0.f, seg) / static_cast<float>(K);
-    const float S = (lqc + beta * (f - mean)) + 0.0f;   // -0 -> +0
-    if (valid) {
-      rows[prow * K + colc] = S;
-      if (out) out[p * K + c] = S;
-    }
-    pos |= valid && S > 0.f;
   }
   return pos;
 }
