@@ -325,8 +325,8 @@ GRAFT_API int graft_synth_node_targets(graft_ctx *ctx, int32_t batch, uint64_t s
 /* Stage timing for benchmarks.  graft_profile_begin arms timing of the next
  * max_calls calls of graft_build_tree and of graft_accept (each counted
  * separately): timing-only HIP events (no system-scope fence) are recorded on
- * the call's stream around every stage, 0 = logits pass, 1 = hidden-state
- * cosines, edge scoring and the SABA budget, 2 = selection, emission and mask,
+ * the call's stream around every stage, 0 = logits pass and hidden-state
+ * cosines, 1 = edge scoring and the SABA budget, 2 = selection, emission and mask,
  * 3 = acceptance (with the fused path of graft_set_fusion, edge scoring and
  * the budget are timed in stage 2).  graft_profile_end synchronizes the events, writes
  * the summed milliseconds stage_ms[4] and the number of timed launches

@@ -149,19 +149,12 @@ int build_tree_with(graft_ctx *ctx, const graft_round_in *in, const graft_tree_o
   hipEvent_t *ev = nullptr;
   if (ctx->prof_build && ctx->prof_nbuild < ctx->prof_cap) ev = ctx->prof_build + 4 * ctx->prof_nbuild++;
   if (ev) (void)hipEventRecord(ev[0], s);
-  hipError_t e = graft::launch_logits_pass(ctx, ws, in->batch, in->logits, out, s);
+  hipError_t e = graft::launch_logits_pass(ctx, ws, in, out, s);
   if (e != hipSuccess) {
     snprintf(what, sizeof what, "%s: logits pass", who);
     return hip_fail(e, what);
   }
   if (ev) (void)hipEventRecord(ev[1], s);
-  if (in->hidden) {
-    e = graft::launch_degen(ctx, ws, in->batch, in->hidden, in->hidden_dim, out->adj_cos, s);
-    if (e != hipSuccess) {
-      snprintf(what, sizeof what, "%s: hidden-state cosines", who);
-      return hip_fail(e, what);
-    }
-  }
   if (!graft::edges_fused(ctx)) e = graft::launch_edge_scores(ctx, ws, in, out, s);
   if (e != hipSuccess) {
     snprintf(what, sizeof what, "%s: edge scores and budget", who);

@@ -285,13 +285,11 @@ struct graft_tdes {
 namespace graft {
 
 // Launchers (stream-ordered, no synchronization).  They return hipError_t.
-hipError_t launch_logits_pass(graft_ctx *ctx, const RoundScratch &ws, int batch,
-                              const uint16_t *logits, const graft_tree_out *out,
-                              hipStream_t stream);
+// The logits pass, with the cosines of adjacent hidden states when the round has
+// them.
+hipError_t launch_logits_pass(graft_ctx *ctx, const RoundScratch &ws, const graft_round_in *in,
+                              const graft_tree_out *out, hipStream_t stream);
 hipError_t launch_projection(graft_ctx *ctx, const graft_scorer_desc *d, hipStream_t stream);
-hipError_t launch_degen(graft_ctx *ctx, const RoundScratch &ws, int batch,
-                        const uint16_t *hidden, int hidden_dim, float *adj_cos_out,
-                        hipStream_t stream);
 hipError_t launch_edge_scores(graft_ctx *ctx, const RoundScratch &ws, const graft_round_in *in,
                               const graft_tree_out *out, hipStream_t stream);
 hipError_t launch_select(graft_ctx *ctx, const RoundScratch &ws, const graft_round_in *in,

@@ -35,6 +35,7 @@
 #include <algorithm>
 #include <type_traits>
 
+#include "degen_device.h"
 #include "graft_internal.h"
 
 namespace graft {
@@ -758,8 +759,14 @@ __device__ __forceinline__ void loose_stats(float x, bool valid, LaneStats &st) 
 template <int CAP, int W>
 __global__ void __launch_bounds__(W * kWave, 4)
 short_pass_kernel(const uint16_t *__restrict__ logits, int V, int splits, int K,
-                  double *__restrict__ part_stats, uint64_t *__restrict__ part_keys, RowOut out) {
+                  double *__restrict__ part_stats, uint64_t *__restrict__ part_keys, RowOut out,
+                  DegenArgs degen) {
   __shared__ PassMem<CAP, W> s;
+  if (blockIdx.x >= degen.first) {   // a run of hidden-state cosines (degen_device.h)
+    __shared__ double s_part[W][kDegenAcc];
+    degen_run<W>(degen, blockIdx.x - degen.first, s_part);
+    return;
+  }
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
   const int lane = lane_id();
   const int64_t row = blockIdx.x / splits;
@@ -872,8 +879,14 @@ template <int CAP, int W>
 __global__ void __launch_bounds__(W * kWave, 4)
 logits_pass_kernel(const uint16_t *__restrict__ logits, int V, int splits, int K,
                    double *__restrict__ part_stats, uint64_t *__restrict__ part_keys,
-                   RowOut out) {
+                   RowOut out,
+                  DegenArgs degen) {
   __shared__ PassMem<CAP, W> s;
+  if (blockIdx.x >= degen.first) {   // a run of hidden-state cosines (degen_device.h)
+    __shared__ double s_part[W][kDegenAcc];
+    degen_run<W>(degen, blockIdx.x - degen.first, s_part);
+    return;
+  }
 
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
   const int lane = lane_id();
@@ -1074,9 +1087,10 @@ int logits_part_slots(const graft_dims &d) {
   return static_cast<int>(best > 0 ? best : 1);
 }
 
-hipError_t launch_logits_pass(graft_ctx *ctx, const RoundScratch &ws, int batch,
-                              const uint16_t *logits, const graft_tree_out *out,
-                              hipStream_t stream) {
+hipError_t launch_logits_pass(graft_ctx *ctx, const RoundScratch &ws, const graft_round_in *in,
+                              const graft_tree_out *out, hipStream_t stream) {
+  const int batch = in->batch;
+  const uint16_t *logits = in->logits;
   const graft_dims &d = ctx->dims;
   const int rows = batch * d.num_pos;
   const int splits = logits_splits(d, rows);
@@ -1091,12 +1105,25 @@ hipError_t launch_logits_pass(graft_ctx *ctx, const RoundScratch &ws, int batch,
   o.o_lse = out ? out->row_lse : nullptr;
   o.o_maxprob = out ? out->row_maxprob : nullptr;
   o.o_ent = out ? out->row_entropy : nullptr;
-  const dim3 grid(static_cast<unsigned>(rows * splits));
+  // the rows' blocks first, then the runs of hidden-state cosines
+  DegenArgs dg{};
+  dg.first = static_cast<unsigned>(rows * splits);
+  unsigned extra = 0;
+  if (in->hidden && d.num_pos > 1) {
+    dg.hidden = in->hidden;
+    dg.L = d.num_pos;
+    dg.H = in->hidden_dim;
+    dg.runs = (d.num_pos - 1 + kDegenPairs - 1) / kDegenPairs;
+    dg.adj_cos = ws.adj_cos;
+    dg.adj_cos_out = out ? out->adj_cos : nullptr;
+    extra = static_cast<unsigned>(batch * dg.runs);
+  }
+  const dim3 grid(dg.first + extra);
   const int V = d.vocab;
   const int waves = logits_waves(rows);
   auto pass = [&](auto kernel) {
     hipLaunchKernelGGL(kernel, grid, dim3(waves * kWave), 0, stream, logits, V, splits, d.top_k,
-                       ws.part_stats, ws.part_keys, o);
+                       ws.part_stats, ws.part_keys, o, dg);
   };
   const bool brief = (V / 8 + splits - 1) / splits <= waves * kTileVec;
   auto by_waves = [&](auto cap) {
