@@ -17,8 +17,9 @@
 // offered to the wave's candidate buffer (ballot/mbcnt appends, a wave bitonic
 // sort of (value desc, id asc) keys when full) only when the ring fills and at
 // the end.  Thresholds come from a radix selection over 16-bit ordered values
-// (one ballot a bit), and the block's survivors are ranked by counting: sorting
-// in their place made up a quarter of the pass's VALU work.
+// (one ballot a bit), and the block's survivors are ranked by counting; with
+// bitonic sorts in their place the pass issued 9.20 VALU instructions per element
+// and lane instead of 8.07 (4096 rows of 151936, K = 32).
 // Where few long rows leave the chip idle, a row is split over several
 // workgroups whose partial results a second small kernel merges.
 //
