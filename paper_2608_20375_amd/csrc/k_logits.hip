@@ -47,7 +47,7 @@ constexpr int kTileVec = kWave * kUnroll;         // 256 vectors = 2048 elements
 constexpr float kL2E = 1.44269504088896340736f;
 constexpr double kLn2 = 0.693147180559945309417232121458;
 constexpr double kLog2e = 1.44269504088896340735992468100;
-constexpr float kNegBig = -1e30f;                 // finite stand-in for -inf
+constexpr float kNegBig = -1e30f;                 // offset of softmax sums without an element
 constexpr int kCus = 256;                         // compute units of the chip
 constexpr int kMinSplitVec = 1024;                // >= 8192 elements per split
 constexpr int kMaxSplits = 32;                    // blocks a row may be split over
@@ -802,10 +802,11 @@ short_pass_kernel(const uint16_t *__restrict__ logits, int V, int splits, int K,
     s.n_list = 0;
   }
 
-  float g[kUnroll], own = kNegBig;
+  // (-inf, no finite value, past the end: a masked logit may be as low as any)
+  float g[kUnroll], own = -INFINITY;
 #pragma unroll
   for (int u = 0; u < kUnroll; ++u) {
-    g[u] = kNegBig;
+    g[u] = -INFINITY;
     if (u < nu && wb + u * kWave + lane < we) g[u] = group_max(q[u]);   // else past the end
     own = fmaxf(own, g[u]);
   }
@@ -818,8 +819,7 @@ short_pass_kernel(const uint16_t *__restrict__ logits, int V, int splits, int K,
   if (n_loose > 0) loose_stats(lx, lvalid, st);
   put_stats<CAP, W>(s, st, wave);
   __syncthreads();
-  float thr = min_bound<W>(s.bound);
-  if (thr < -1e29f) thr = -INFINITY;   // fewer than K real elements seen
+  const float thr = min_bound<W>(s.bound);   // -inf: fewer than K elements seen
   const int64_t slot = row * splits + split;
   // a lane's elements that reach it, as bits u * 8 + e; one scan and one LDS
   // atomic place the wave's keys
@@ -929,9 +929,11 @@ logits_pass_kernel(const uint16_t *__restrict__ logits, int V, int splits, int K
   // (two tiles with 4 waves, whose first tiles hold few of the row).  With 4
   // waves the K-th largest of the 256 lane maxima; with more the smallest of
   // the waves' ceil(K / W)-th ones.  Either way K elements reach it, so it is
-  // a lower bound of the chunk's K-th largest value.
+  // a lower bound of the chunk's K-th largest value; a lane with no element
+  // holds -inf, which every later bound exceeds (a finite stand-in would pass
+  // for a logit in rows masked with large negative values).
   {
-    float tm = kNegBig;
+    float tm = -INFINITY;
 #pragma unroll
     for (int u = 0; u < kUnroll; ++u) {
       if (one) tm = fmaxf(tm, group_max(cur[u]));
@@ -952,7 +954,6 @@ logits_pass_kernel(const uint16_t *__restrict__ logits, int V, int splits, int K
       __syncthreads();
       w.thr = min_bound<W>(s.bound);
     }
-    if (w.thr < -1e29f) w.thr = -INFINITY;   // fewer than K real elements seen
   }
   if (partial) {
     const float g = pvalid ? group_max(extra) : kNegBig;

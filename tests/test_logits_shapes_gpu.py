@@ -1,7 +1,7 @@
 """The logits pass at the edges of its block shapes: rows that just fit one tile
 a wave and that just do not, four- and eight-wave blocks, rows split over blocks,
 misaligned rows, and rows of equal logits, whose candidates overflow the block's
-list.  Against float64 sums and a sort by (logit descending, id ascending).
+list, and rows masked with large negative values.  Against float64 sums and a sort by (logit descending, id ascending).
 
 Tolerances: ids exact.  log q, lse and the entropy are fp64 sums of fp32
 exponentials (2^-22 relative each) rounded to fp32; 1e-5 relative with a floor of
@@ -49,20 +49,9 @@ def draw(kind, rows, V, seed):
     return torch.from_numpy(x).to(torch.bfloat16)
 
 
-@pytest.mark.parametrize("batch,L,V,K,kind", SHAPES)
-@pytest.mark.parametrize("static", [False, True])
-def test_logits_shapes(batch, L, V, K, kind, static):
-    import paper_2608_20375_amd as G
-    print("batch", batch, "L", L, "V", V, "K", K, kind, static, flush=True)
-    rows = batch * L
-    x = draw(kind, rows, V, 77 + V + K).cuda()
-    ctx = G.Context(batch, L, V, K, 8)
-    emb = torch.zeros(V, 4, device="cuda")
-    g = torch.zeros(4, 4, device="cuda")
-    ctx.set_scorer(emb, g, g)
-    zeros = torch.zeros(batch, dtype=torch.int32, device="cuda")
-    out = ctx.build_tree(x.view(batch, L, V), zeros, zeros, fixed_budget=zeros + 1,
-                         static_scratch=static)
+def check_rows(G, ctx, x, K, out):
+    """Candidates and statistics of the rows x [rows, V] against float64 and a stable sort."""
+    rows = x.shape[0]
     d = x.double()
     lse = torch.logsumexp(d, -1)
     lp = d - lse[:, None]
@@ -78,4 +67,63 @@ def test_logits_shapes(batch, L, V, K, kind, static):
         err = np.abs(got.double().cpu().numpy() - ref)
         assert (err <= 1e-6 + 1e-5 * np.abs(ref)).all()
     assert ctx.device_status() == 0
+
+
+def context(G, batch, L, V, K):
+    ctx = G.Context(batch, L, V, K, 8)
+    emb = torch.zeros(V, 4, device="cuda")
+    g = torch.zeros(4, 4, device="cuda")
+    ctx.set_scorer(emb, g, g)
+    return ctx
+
+
+@pytest.mark.parametrize("batch,L,V,K,kind", SHAPES)
+@pytest.mark.parametrize("static", [False, True])
+def test_logits_shapes(batch, L, V, K, kind, static):
+    import paper_2608_20375_amd as G
+    print("batch", batch, "L", L, "V", V, "K", K, kind, static, flush=True)
+    rows = batch * L
+    x = draw(kind, rows, V, 77 + V + K).cuda()
+    ctx = context(G, batch, L, V, K)
+    zeros = torch.zeros(batch, dtype=torch.int32, device="cuda")
+    out = ctx.build_tree(x.view(batch, L, V), zeros, zeros, fixed_budget=zeros + 1,
+                         static_scratch=static)
+    check_rows(G, ctx, x, K, out)
+    ctx.close()
+
+
+MASKED = [
+    # batch, L, V, K
+    (1, 3, 16384, 13),       # one tile a wave, 8 waves
+    (27, 19, 8191, 40),      # one tile a wave, 4 waves
+    (2, 3, 16400, 64),       # streamed, 8 waves
+    (27, 19, 9001, 8),       # streamed, 4 waves
+    (1, 3, 98311, 32),       # split, a tile a wave
+    (32, 1, 131080, 16),     # split, streamed; the last split has a wave without a tile
+]
+
+
+@pytest.mark.parametrize("batch,L,V,K", MASKED)
+@pytest.mark.parametrize("allowed", ["one", "few", "all but one of K"])
+@pytest.mark.parametrize("mask", [-1e30, -1e32])
+def test_masked_rows(batch, L, V, K, allowed, mask):
+    """Constrained decoding: fewer than K words are allowed and the others hold a large
+    negative finite logit, so masked words in id order fill the list."""
+    import paper_2608_20375_amd as G
+    print("masked", batch, L, V, K, allowed, mask, flush=True)
+    rows = batch * L
+    n = {"one": 1, "few": 3}.get(allowed, K - 1)
+    g = np.random.default_rng(V + n)
+    x = np.full((rows, V), mask, np.float32)
+    for r in range(rows):
+        # the allowed words spread, or at the row's ends, or together
+        ids = (g.choice(V, n, replace=False), np.r_[V - 1, np.arange(n - 1)],
+               V // 2 + np.arange(n))[r % 3]
+        x[r, ids] = g.standard_normal(n) * 3
+    x = torch.from_numpy(x).to(torch.bfloat16).cuda()
+    ctx = context(G, batch, L, V, K)
+    zeros = torch.zeros(batch, dtype=torch.int32, device="cuda")
+    out = ctx.build_tree(x.view(batch, L, V), zeros, zeros, fixed_budget=zeros + 8)
+    check_rows(G, ctx, x, K, out)
+    assert (out.n_nodes == 8).all()
     ctx.close()
