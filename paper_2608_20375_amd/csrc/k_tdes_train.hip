@@ -28,7 +28,10 @@
 //   and two items a wave.
 // wgrad_kernel: the two contractions on MFMA, 4 rows per instruction; a wave owns
 //   a tile of the gradient and goes through all rows of its block, 12 steps'
-//   loads at a time, so nothing is summed across waves; per-block partials.
+//   loads at a time, so nothing is summed across waves; six steps' products join
+//   the block's sum at a time, which keeps its fp32 rounding below that of one long
+//   chain (G = P = 4096: 2.3e-7 of the gradient's norm in one chain, 2.1e-7 so);
+//   per-block partials.
 // G = P = 4096, E = 128, m = 32, K = 16 (us): loss 28.6 -> 25.9, wgrad 22.0 (K rows
 //   a group, a tile of rows a wave, waves summed through LDS) -> 9.9, step 52.4 ->
 //   38.6; G = P = 512, E = 64, m = 16, K = 8: wgrad 8.6 -> 4.4, step 23.3 -> 18.9.
@@ -47,6 +50,10 @@ constexpr int kGradWaves = 8;
 constexpr int kGradThreads = kGradWaves * kWave;
 constexpr int kGradTarget = 256;      // wgrad blocks: one a CU
 constexpr int kGradBatch = 12;        // 4-row steps loaded together
+constexpr int kGradChain = 6;         // steps summed before they join the block's fp32 sum
+constexpr int kMaxGradRows = 384;     // rows a wgrad block takes at the most
+static_assert(kGradBatch % kGradChain == 0 && kMaxGradRows <= kGradThreads,
+              "whole chains a batch, a token slot a row");
 constexpr int kMinGradRows = 16;      // rows a wgrad block takes at the least
 constexpr int kMaxEM = 4096;          // E * M16, M16 = m rounded up to 16
 constexpr int kMaxLM = 1024;          // L * M16
@@ -634,47 +641,52 @@ wgrad_kernel(TrainArgs a, int child_blocks, int block_rows) {
   for (int nt = 0; nt < NT; ++nt) acc[nt] = v4f{0.0f, 0.0f, 0.0f, 0.0f};
   const int64_t first = static_cast<int64_t>(blk) * block_rows;
   const int64_t last = first + block_rows < rows ? first + block_rows : rows;
-  for (int64_t r0 = first; r0 < last; r0 += kGradThreads) {
-    // the tokens of up to kGradThreads rows in one round trip; -1: no row, -2: a
-    // group's own sum
-    const int64_t r = r0 + tid;
-    int tok = -1;
-    if (r < last) {
-      if (r >= a.G) {
-        const int64_t e = r - a.G;
-        tok = a.pairs[(e >> 1) * 6 + 3 * (e & 1) + (side == 0 ? 1 : 0)];
-      } else {
-        tok = side == 0 ? -2 : a.parent[r];
-      }
-      if (tok != -2 && (tok < 0 || tok >= a.V)) tok = -1;
+  // the tokens of the rows in one round trip; -1: no row, -2: a group's own sum
+  const int64_t r = first + tid;
+  int tok = -1;
+  if (r < last) {
+    if (r >= a.G) {
+      const int64_t e = r - a.G;
+      tok = a.pairs[(e >> 1) * 6 + 3 * (e & 1) + (side == 0 ? 1 : 0)];
+    } else {
+      tok = side == 0 ? -2 : a.parent[r];
     }
-    if (r0 != first) __syncthreads();
-    s_tok[tid] = tok;
-    __syncthreads();
-    const int n = last - r0 < kGradThreads ? static_cast<int>(last - r0) : kGradThreads;
-    // kGradBatch steps at a time, every load issued before the first product
-    for (int s0 = 4 * rg; s0 < n; s0 += 4 * RG * kGradBatch) {
-      float ev[kGradBatch], av[kGradBatch][NT];
+    if (tok != -2 && (tok < 0 || tok >= a.V)) tok = -1;
+  }
+  s_tok[tid] = tok;
+  __syncthreads();
+  const int n = static_cast<int>(last - first);
+  // kGradBatch steps at a time, every load issued before the first product
+  for (int s0 = 4 * rg; s0 < n; s0 += 4 * RG * kGradBatch) {
+    float ev[kGradBatch], av[kGradBatch][NT];
 #pragma unroll
-      for (int j = 0; j < kGradBatch; ++j) {
-        if (s0 + 4 * RG * j >= n) break;   // uniform in the wave
-        const int st = s0 + 4 * RG * j + q;
-        const int tk = s_tok[st < kGradThreads ? st : 0];
-        const bool live = st < n && tk != -1;
-        const int64_t row = live ? r0 + st : 0;
-        const float *er = live && tk == -2 ? a.wsum + row * E
-                                           : a.emb + static_cast<int64_t>(live ? tk : 0) * E;
-        const float *yr = dy + row * M16 + c16;
-        ev[j] = live ? er[kt * 16 + c16] : 0.0f;
+    for (int j = 0; j < kGradBatch; ++j) {
+      if (s0 + 4 * RG * j >= n) break;   // uniform in the wave
+      const int st = s0 + 4 * RG * j + q;
+      const int tk = s_tok[st < kGradThreads ? st : 0];
+      const bool live = st < n && tk != -1;
+      const int64_t row = live ? first + st : 0;
+      const float *er = live && tk == -2 ? a.wsum + row * E
+                                         : a.emb + static_cast<int64_t>(live ? tk : 0) * E;
+      const float *yr = dy + row * M16 + c16;
+      ev[j] = live ? er[kt * 16 + c16] : 0.0f;
 #pragma unroll
-        for (int nt = 0; nt < NT; ++nt) av[j][nt] = live ? yr[nt * 16] : 0.0f;
-      }
+      for (int nt = 0; nt < NT; ++nt) av[j][nt] = live ? yr[nt * 16] : 0.0f;
+    }
 #pragma unroll
-      for (int j = 0; j < kGradBatch; ++j) {
+    for (int h = 0; h < kGradBatch; h += kGradChain) {
+      if (s0 + 4 * RG * h >= n) break;
+      v4f part[NT];
+#pragma unroll
+      for (int nt = 0; nt < NT; ++nt) part[nt] = v4f{0.0f, 0.0f, 0.0f, 0.0f};
+#pragma unroll
+      for (int j = h; j < h + kGradChain; ++j) {
         if (s0 + 4 * RG * j >= n) break;
 #pragma unroll
-        for (int nt = 0; nt < NT; ++nt) acc[nt] = mfma(av[j][nt], ev[j], acc[nt]);
+        for (int nt = 0; nt < NT; ++nt) part[nt] = mfma(av[j][nt], ev[j], part[nt]);
       }
+#pragma unroll
+      for (int nt = 0; nt < NT; ++nt) acc[nt] += part[nt];
     }
   }
   const int m = a.m, em = E * m;
@@ -833,10 +845,12 @@ TdesPlan tdes_plan(const graft_tdes_dims &d, int G, int P) {
   // with more
   const int most = d.top_k <= 16 ? 768 : 512;
   p.loss_blocks = static_cast<int>(lb < 1 ? 1 : lb > most ? most : lb);
-  // as many rows a block as give each CU one
+  // as many rows a block as give each CU one, up to kMaxGradRows: a block's sum is
+  // fp32 (chains of 24 rows, then at most 16 of them: 40 additions, however large the
+  // batch), the blocks' are added in fp64
   const int64_t rows = static_cast<int64_t>(G) + 2 * static_cast<int64_t>(P);   // of each side
   const int64_t per = ((2 * rows + kGradTarget - 1) / kGradTarget + 3) / 4 * 4;
-  p.grad_rows = static_cast<int>(per < kMinGradRows ? kMinGradRows : per);
+  p.grad_rows = static_cast<int>(per < kMinGradRows ? kMinGradRows : per > kMaxGradRows ? kMaxGradRows : per);
   p.child_blocks = p.parent_blocks = static_cast<int>((rows + p.grad_rows - 1) / p.grad_rows);
   return p;
 }
@@ -844,9 +858,12 @@ TdesPlan tdes_plan(const graft_tdes_dims &d, int G, int P) {
 TdesWorkspace tdes_workspace(const graft_tdes_dims &d) {
   const int64_t m16 = (d.score_dim + 15) / 16 * 16;
   const int64_t rows = static_cast<int64_t>(d.max_groups) + 2 * static_cast<int64_t>(d.max_pairs);
-  // a side has at most kGradTarget / 2 + 1 blocks, and one per kMinGradRows rows
+  // a side has at most one block per kMinGradRows rows, and kGradTarget / 2 + 1 or
+  // one per kMaxGradRows rows if that is more
   int64_t blocks = (rows + kMinGradRows - 1) / kMinGradRows;
-  if (blocks > kGradTarget / 2 + 1) blocks = kGradTarget / 2 + 1;
+  int64_t most = (rows + kMaxGradRows - 1) / kMaxGradRows;
+  if (most < kGradTarget / 2 + 1) most = kGradTarget / 2 + 1;
+  if (blocks > most) blocks = most;
   TdesWorkspace w;
   const int loss = tdes_plan(d, d.max_groups, d.max_pairs).loss_blocks;   // grows with the batch
   auto whole = [](int64_t n) { return (n + 63) / 64 * 64; };   // parts start on 256-byte boundaries

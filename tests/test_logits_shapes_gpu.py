@@ -1,7 +1,8 @@
 """The logits pass at the edges of its block shapes: rows that just fit one tile
 a wave and that just do not, four- and eight-wave blocks, rows split over blocks,
-misaligned rows, and rows of equal logits, whose candidates overflow the block's
-list, and rows masked with large negative values.  Against float64 sums and a sort by (logit descending, id ascending).
+misaligned rows, rows of equal logits, whose candidates overflow the block's list,
+and rows masked with large negative values.  Against float64 sums and a sort by
+(logit descending, id ascending).
 
 Tolerances: ids exact.  log q, lse and the entropy are fp64 sums of fp32
 exponentials (2^-22 relative each) rounded to fp32; 1e-5 relative with a floor of
