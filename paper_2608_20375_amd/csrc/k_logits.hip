@@ -509,9 +509,9 @@ __device__ __forceinline__ void lanes_merge(bool on, float &mL, double &S, doubl
 #pragma unroll
   for (int o = 1; o < N; o <<= 1)
     m = fmaxf(m, __uint_as_float(xor_lane(__float_as_uint(m), o)));
-  const float d = on ? mL - m : 0.f;
-  const double a = static_cast<double>(__builtin_amdgcn_exp2f(d));
-  T2 = on ? a * (T2 + static_cast<double>(d) * S) : 0.0;
+  const double d = on ? static_cast<double>(mL) - static_cast<double>(m) : 0.0;
+  const double a = static_cast<double>(__builtin_amdgcn_exp2f(static_cast<float>(d)));
+  T2 = on ? a * (T2 + d * S) : 0.0;
   S = on ? a * S : 0.0;
 #pragma unroll
   for (int o = 1; o < N; o <<= 1) {
