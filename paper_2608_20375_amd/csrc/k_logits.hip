@@ -611,12 +611,44 @@ struct PassMem {
   double S[4 * W], T2[4 * W];   // per row of 16 lanes
   float mL[W];
   double fin[4];              // the chunk's mL, S, T2, and lse
-  uint32_t lmax[W == 4 ? W * kWave : 1];   // lane maxima of the first tiles
+  uint32_t lmax[W * kWave];   // lane maxima: all of a short chunk, a long one's first tiles
   uint32_t bound[W];          // per wave: ceil(K / W) of its values reach this (ordered key)
   uint32_t thr;               // largest published threshold, ordered key
   int cnt[W];
   int n_short, n_list;        // keys in list: of a short chunk, of the buffers
 };
+
+// A lower bound of the chunk's K-th largest value from the lanes' maxima (lmax,
+// then a barrier): K distinct lanes reach the K-th largest of them.  Over the whole
+// block, since words ordered by frequency put the largest logits of a row into one
+// wave's share.  Where every lane holds elements (full), formed from the maxima of
+// 256 groups of lanes across the waves, up to 16 candidates of 128, which takes
+// fewer ballots; else the groups could be fewer than K.
+// Against the smallest of the eight waves' own ceil(K / 8)-th maxima, which lets a
+// hundred and more keys through on ordered words (us; logit = 2 normal -
+// log(rank)): 16 rows of 8000, K = 8 11.9 -> 7.4, K = 64 25.4 -> 10.2, 512 rows of
+// 32000, K = 64 34.1 -> 22.0; on exchangeable ones: 16 rows of 32000, K = 8 10.8 ->
+// 10.4, 512 of 151936, K = 64 38.8 -> 39.0, one of 32000, K = 64 12.5 -> 12.8.
+template <int CAP, int W>
+__device__ __forceinline__ float lanes_kth(const PassMem<CAP, W> &s, int K, bool full) {
+  const int lane = lane_id();
+  uint32_t k[W];
+#pragma unroll
+  for (int i = 0; i < W; ++i) k[i] = s.lmax[i * kWave + lane];
+  if (full) {
+    uint32_t g[4];
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+      g[i] = k[i];
+#pragma unroll
+      for (int j = i + 4; j < W; j += 4) g[i] = g[i] > k[j] ? g[i] : k[j];
+    }
+    if (K > 16) return wave_kth_bf16<4>(g, K);
+    const uint32_t h[2] = {g[0] > g[2] ? g[0] : g[2], g[1] > g[3] ? g[1] : g[3]};
+    return wave_kth_bf16<2>(h, K);
+  }
+  return wave_kth_bf16<W>(k, K);
+}
 
 template <int CAP, int W>
 __device__ __forceinline__ void put_stats(PassMem<CAP, W> &s, LaneStats &st, int wave) {
@@ -754,8 +786,8 @@ __device__ __forceinline__ void loose_stats(float x, bool valid, LaneStats &st) 
 }
 
 // A chunk of at most one tile a wave: divided evenly over the W waves, all of it
-// loaded at once and kept in registers.  Latency-bound: the waves' bounds and
-// statistics meet at one barrier, then the few keys that reach the threshold go
+// loaded at once and kept in registers.  Latency-bound: the lanes' maxima and the
+// waves' statistics meet at one barrier, then the few keys that reach the threshold go
 // straight to the block's list and are ranked after a second one.
 template <int CAP, int W>
 __global__ void __launch_bounds__(W * kWave, 4)
@@ -810,8 +842,8 @@ short_pass_kernel(const uint16_t *__restrict__ logits, int V, int splits, int K,
     if (u < nu && wb + u * kWave + lane < we) g[u] = group_max(q[u]);   // else past the end
     own = fmaxf(own, g[u]);
   }
-  const float bound = wave_kth_bf16(ordered_f32(own) >> 16, (K + W - 1) / W);
-  if (lane == 0) s.bound[wave] = ordered_f32(bound);
+  s.lmax[wave * kWave + lane] = ordered_f32(own) >> 16;
+  if (lane == 0) s.bound[wave] = ordered_f32(-INFINITY);
   stats_raise(st, fmaxf(own, lx));
 #pragma unroll
   for (int u = 0; u < kUnroll; ++u)
@@ -819,7 +851,7 @@ short_pass_kernel(const uint16_t *__restrict__ logits, int V, int splits, int K,
   if (n_loose > 0) loose_stats(lx, lvalid, st);
   put_stats<CAP, W>(s, st, wave);
   __syncthreads();
-  const float thr = min_bound<W>(s.bound);   // -inf: fewer than K elements seen
+  const float thr = lanes_kth<CAP, W>(s, K, c.n_vec >= W * kWave);   // -inf: fewer than K lanes
   const int64_t slot = row * splits + split;
   // a lane's elements that reach it, as bits u * 8 + e; one scan and one LDS
   // atomic place the wave's keys
@@ -926,12 +958,9 @@ logits_pass_kernel(const uint16_t *__restrict__ logits, int V, int splits, int K
   }
   load_tile(c.vec, two ? t + W : t0, nxt);
   // Initial threshold, block wide, from the lanes' maxima over the first tile
-  // (two tiles with 4 waves, whose first tiles hold few of the row).  With 4
-  // waves the K-th largest of the 256 lane maxima; with more the smallest of
-  // the waves' ceil(K / W)-th ones.  Either way K elements reach it, so it is
-  // a lower bound of the chunk's K-th largest value; a lane with no element
-  // holds -inf, which every later bound exceeds (a finite stand-in would pass
-  // for a logit in rows masked with large negative values).
+  // (two tiles with 4 waves, whose first tiles hold few of the row).  A lane with
+  // no element holds -inf, which every later bound exceeds (a finite stand-in would
+  // pass for a logit in rows masked with large negative values).
   {
     float tm = -INFINITY;
 #pragma unroll
@@ -940,20 +969,10 @@ logits_pass_kernel(const uint16_t *__restrict__ logits, int V, int splits, int K
       if (W == 4 && two) tm = fmaxf(tm, group_max(nxt[u]));
     }
     if (partial && pvalid) tm = fmaxf(tm, group_max(extra));
-    if constexpr (W == 4) {
-      s.lmax[wave * kWave + lane] = ordered_f32(tm) >> 16;
-      if (lane == 0) s.bound[wave] = ordered_f32(-INFINITY);
-      __syncthreads();
-      uint32_t k4[W];
-#pragma unroll
-      for (int i = 0; i < W; ++i) k4[i] = s.lmax[i * kWave + lane];
-      w.thr = wave_kth_bf16<W>(k4, K);
-    } else {
-      const float bound = wave_kth_bf16(ordered_f32(tm) >> 16, (K + W - 1) / W);
-      if (lane == 0) s.bound[wave] = ordered_f32(bound);
-      __syncthreads();
-      w.thr = min_bound<W>(s.bound);
-    }
+    s.lmax[wave * kWave + lane] = ordered_f32(tm) >> 16;
+    if (lane == 0) s.bound[wave] = ordered_f32(-INFINITY);
+    __syncthreads();
+    w.thr = lanes_kth<CAP, W>(s, K, n_full >= W);
   }
   if (partial) {
     const float g = pvalid ? group_max(extra) : kNegBig;

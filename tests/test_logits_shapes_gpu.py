@@ -36,6 +36,16 @@ SHAPES = [
     (1, 2, 120000, 48, "equal"),        # split: every partial list is a tie
     (1, 3, 20011, 64, "levels"),        # four values only
     (1, 3, 120011, 17, "levels"),
+    (1, 3, 16384, 4, "ordered"),        # the largest logits in one wave's share, most
+    (2, 3, 8000, 64, "ordered"),        # of them in a few lanes: one tile a wave
+    (27, 19, 8191, 40, "ordered"),
+    (1, 3, 33000, 16, "ordered"),       # streamed: candidates of 128, 256 groups of lanes
+    (1, 3, 33000, 17, "ordered"),
+    (27, 19, 9000, 64, "ordered"),
+    (1, 3, 151936, 64, "ordered"),      # split: one partial list holds the row's best
+    (32, 1, 131080, 16, "normal"),      # split: the last split has a wave without a tile
+    (1, 2, 100, 16, "normal"),          # fewer lanes with elements than candidates
+    (1, 2, 1000, 64, "normal"),
 ]
 
 
@@ -43,11 +53,13 @@ def draw(kind, rows, V, seed):
     g = np.random.default_rng(seed)
     if kind == "equal":
         x = np.full((rows, V), -1.5, np.float32)
+    elif kind == "ordered":   # words by frequency
+        x = 2 * g.standard_normal((rows, V), dtype=np.float32) - np.log(np.arange(V) + 10.0)
     elif kind == "levels":
         x = g.integers(-2, 2, (rows, V)).astype(np.float32)
     else:
         x = g.standard_normal((rows, V), dtype=np.float32) * 3
-    return torch.from_numpy(x).to(torch.bfloat16)
+    return torch.from_numpy(x.astype(np.float32)).to(torch.bfloat16)
 
 
 def check_rows(G, ctx, x, K, out):
