@@ -1085,11 +1085,19 @@ merge_kernel(int splits, int K, const double *__restrict__ part_stats,
 
 // Waves of a block.  Up to 512 rows eight: half as many rows in flight as with
 // four, with half the work each (256 rows of 151936: 20.5 us against 21.6; 16
-// rows of 32000: 9.9 against 10.5).  Above that four waves keep the chip as full
-// and finish a row's end beside three other rows of the CU (512 rows of 32000:
-// 14.2 us against 14.8; 640 rows of 128256: 34.8 against 37.4; 1024: 46.0
-// against 49.2).  Sixteen lost everywhere (256 rows: 21.2; 512: 60 against 39).
-static int logits_waves(int rows) { return rows > 2 * kCus ? 4 : 8; }
+// rows of 32000: 9.9 against 10.5; at 512 rows within 4% of each other: 128256, K =
+// 8 27.7 against 28.5, 151936, K = 32 35.7 against 35.1).  Above that four waves
+// keep the chip as full and finish a row's end beside three other rows of the CU
+// (640 rows of 128256: 34.8 us against 37.4; 1024: 46.0 against 49.2).  Sixteen lost
+// everywhere (256 rows: 21.2; 512: 60 against 39).  Rows that four waves take in one
+// tile each leave eight too little: above one row a CU they take four (512 rows of
+// 4100, K = 8: 8.5 us against 9.1; 256 rows 7.8 against 8.0), and rows of one vector
+// a lane at any number (one row of 1000, K = 16: 7.1 against 7.5; 512 rows, K = 64:
+// 10.6 against 14.4).
+static int logits_waves(int rows, int vocab) {
+  if (rows > 2 * kCus || (rows > kCus && vocab <= 4 * 8 * kTileVec)) return 4;
+  return vocab <= 4 * 8 * kWave ? 4 : 8;
+}
 
 // Blocks a row is split over: one block a CU, where the rows leave at least three
 // of four CUs idle and a row has more than six tiles a wave.  A split halves the
@@ -1150,7 +1158,7 @@ hipError_t launch_logits_pass(graft_ctx *ctx, const RoundScratch &ws, const graf
   }
   const dim3 grid(dg.first + extra);
   const int V = d.vocab;
-  const int waves = logits_waves(rows);
+  const int waves = logits_waves(rows, V);
   auto pass = [&](auto kernel) {
     hipLaunchKernelGGL(kernel, grid, dim3(waves * kWave), 0, stream, logits, V, splits, d.top_k,
                        ws.part_stats, ws.part_keys, o, dg);
