@@ -239,7 +239,8 @@ GRAFT_API int graft_set_fusion(graft_ctx *ctx, int32_t enable, int32_t *active /
  * SABA parameters, the history ring and the device status.  The bytes needed grow with the batch:
  * 256-byte aligned parts of B*L*K*(4 + 4 + 4) + B*L*(12 + 1) + B*L*K*K*4 +
  * 4*B*max(L - 1, 1) bytes, plus 8*(3 + K) bytes per split-row partial when
- * rows are split (up to 64 rows of a vocabulary above 98304).  A batch whose need exceeds
+ * rows are split (into at most 1023 in all, by a rule on their number and the
+ * vocabulary: none below 98305 words or above 384 rows).  A batch whose need exceeds
  * the array returns GRAFT_ERR_UNSUPPORTED before anything is enqueued.  The
  * call allocates nothing (the array's address on each device is resolved
  * once, when a context is created there).  Every call on one GPU shares that

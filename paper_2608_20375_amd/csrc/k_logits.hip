@@ -1094,23 +1094,47 @@ merge_kernel(int splits, int K, const double *__restrict__ part_stats,
 // 4100, K = 8: 8.5 us against 9.1; 256 rows 7.8 against 8.0), and rows of one vector
 // a lane at any number (one row of 1000, K = 16: 7.1 against 7.5; 512 rows, K = 64:
 // 10.6 against 14.4).
-static int logits_waves(int rows, int vocab) {
-  if (rows > 2 * kCus || (rows > kCus && vocab <= 4 * 8 * kTileVec)) return 4;
+static int logits_waves(int rows, int vocab, int splits) {
+  if (rows > 2 * kCus || (rows > kCus && (splits > 1 || vocab <= 4 * 8 * kTileVec))) return 4;
   return vocab <= 4 * 8 * kWave ? 4 : 8;
 }
 
-// Blocks a row is split over: one block a CU, where the rows leave at least three
-// of four CUs idle and a row has more than six tiles a wave.  A split halves the
-// pass but its merge kernel costs about 5 us (16 rows of 151936: 12.5 us over 16
-// blocks, 19 over one; 64 rows: 16.1 over 4, 19 over one; 128 rows: 18.8 over 2,
-// 19.1 over one; of 32000, 65536 and 100277: 9.9, 11.5 and 13.8 over one block,
-// 12.4, 11.7 and 12.0 over many, with K = 32 12.1, 14.6 and 17.0 against 14.4,
-// 15.9 and 17.3).
+// Blocks a row is split over.  A split shortens the longest share of a CU but its
+// merge kernel costs about 5 us, so the words that it takes off that share have to
+// be worth that.
+//   up to 64 rows: one block a CU, for rows of more than six tiles a wave (16 rows of
+// 151936: 12.5 us over 16 blocks, 19 over one; 64 rows: 16.1 over 4, 19 over one; of
+// 32000, 65536 and 100277: 9.9, 11.5 and 13.8 over one block, 12.4, 11.7 and 12.0
+// over many, with K = 32 12.1, 14.6 and 17.0 against 14.4, 15.9 and 17.3)
+//   up to 128: the two or three blocks that give one a CU, where they take six tiles
+// a wave off a block (K = 8, over one block and split: 85 rows of 151936 18.9 and
+// 17.9 us, of 524288 38.3 and 26.9; 128 rows of 151936 18.7 and 19.7, of 200064
+// 21.4 and 21.2, of 524288 39.2 and 32.1)
+//   up to 170: three, two a CU, by the same line (170 rows of 262144 24.9 and 26.3,
+// of 400000 32.7 and 32.4, 129 of 524288 38.7 and 35.5; 171 rows 39.6 and 47.4)
+//   257 to 341: a second row goes to few CUs and the others wait for them.  Three
+// blocks of four waves, four a CU, from 196608 words (300 rows of 200064 33.8 and
+// 31.1 us, of 262144 40.7 and 37.4, with K = 64 48.2 and 48.3, of 524288 73.2 and
+// 60.8)
+//   up to 384: two, three a CU, from 393216 (342 rows of 262144, K = 64 48.8 and
+// 50.1; of 400000, K = 8 58.6 and 53.9)
+// Elsewhere a split gives no CU a smaller share, or costs more than it gives.
 int logits_splits(const graft_dims &d, int rows) {
-  const int64_t nv_row = d.vocab / 8;
-  if (nv_row <= 6 * 8 * kTileVec || rows > kCus / 4) return 1;
-  const int64_t s = kCus / rows, max_s = nv_row / kMinSplitVec;   // max_s >= 12
-  return static_cast<int>(std::min<int64_t>({s, max_s, kMaxSplits}));
+  const int64_t nv_row = d.vocab / 8, round = 8 * kTileVec;   // round: a tile for each of 8 waves
+  if (rows <= kCus / 4) {
+    if (nv_row <= 6 * round) return 1;
+    const int64_t s = kCus / rows, max_s = nv_row / kMinSplitVec;   // max_s >= 12
+    return static_cast<int>(std::min<int64_t>({s, max_s, kMaxSplits}));
+  }
+  if (rows <= kCus / 2) {
+    const int s = kCus / rows;
+    return nv_row * (s - 1) > 6 * round * s ? s : 1;
+  }
+  if (3 * rows <= 2 * kCus) return nv_row > 18 * round ? 3 : 1;
+  if (rows <= kCus) return 1;
+  if (3 * rows <= 4 * kCus) return nv_row > 12 * round ? 3 : 1;
+  if (2 * rows <= 3 * kCus) return nv_row > 24 * round ? 2 : 1;
+  return 1;
 }
 
 int logits_part_slots(const graft_dims &d) {
@@ -1158,7 +1182,7 @@ hipError_t launch_logits_pass(graft_ctx *ctx, const RoundScratch &ws, const graf
   }
   const dim3 grid(dg.first + extra);
   const int V = d.vocab;
-  const int waves = logits_waves(rows, V);
+  const int waves = logits_waves(rows, V, splits);
   auto pass = [&](auto kernel) {
     hipLaunchKernelGGL(kernel, grid, dim3(waves * kWave), 0, stream, logits, V, splits, d.top_k,
                        ws.part_stats, ws.part_keys, o, dg);

@@ -23,11 +23,23 @@ SHAPES = [
     (1, 2, 18433, 33, "normal"),        # the ninth tile
     (1, 64, 98312, 8, "normal"),        # 64 rows above the split line: 4 blocks a row
     (5, 13, 98312, 8, "normal"),        # one row more: not split
+    (5, 13, 147473, 16, "normal"),      # 65 rows just past their line: 3 blocks a row
+    (8, 16, 196625, 40, "normal"),      # 128 rows just past it: 2 blocks
+    (10, 17, 294929, 8, "normal"),      # 170 rows just past it: 3 blocks, two a CU
+    (9, 19, 294929, 8, "normal"),       # 171 rows: not split
+    (257, 1, 196625, 64, "normal"),     # 257 rows: 3 blocks of four waves
+    (31, 11, 196625, 8, "ordered"),     # 341 rows: the same
+    (18, 19, 196625, 8, "normal"),      # 342 rows: not split
+    (18, 19, 393233, 16, "normal"),     # 342 rows: 2 blocks
     (1, 4, 98304, 8, "normal"),         # at the line: not split
     (1, 3, 98311, 32, "normal"),        # split, misaligned, last split short
     (1, 1, 151937, 64, "normal"),       # the most splits a row of this size takes
     (1, 5, 300007, 64, "normal"),       # 32 blocks a row at most
-    (32, 16, 4100, 16, "normal"),       # 512 rows: 8 waves
+    (16, 16, 8192, 16, "normal"),       # 256 rows: 8 waves
+    (32, 16, 8192, 16, "normal"),       # 512 rows of one tile a wave: 4 waves
+    (32, 16, 8200, 16, "normal"),       # 512 rows of more: 8 waves
+    (1, 3, 2048, 40, "normal"),         # one vector a lane: 4 waves
+    (1, 3, 2049, 40, "normal"),         # more: 8 waves
     (27, 19, 8201, 16, "normal"),       # 513 rows: 4 waves, just past one tile a wave
     (27, 19, 8191, 40, "normal"),       # 513 rows: 4 waves, at most one tile a wave
     (1, 2, 16000, 16, "equal"),         # one value: 16000 candidates tie
