@@ -65,9 +65,14 @@ __device__ __forceinline__ double quad_sum_f64(double v) {
 
 // Solves the N x N system M x = r by Gaussian elimination with partial pivoting;
 // false when a pivot is not positive enough.  Fully unrolled: rows are swapped
-// by selects, so everything stays in registers.
-template <int N>
+// by selects, so everything stays in registers.  PLAIN: every operation rounded by
+// itself and true divisions, so that a system of whole numbers whose columns are
+// multiples of each other cancels to a zero pivot (with products by a reciprocal,
+// or fused, a tiny one is left, and an x of 1e15); otherwise one division a pivot,
+// since the step's chain is all latency.
+template <int N, bool PLAIN>
 __device__ __forceinline__ bool solve_small(double (&M)[N][N], double (&r)[N], double (&x)[N]) {
+#pragma clang fp contract(off)
   bool ok = true;
   double inv[N];
 #pragma unroll
@@ -96,21 +101,21 @@ __device__ __forceinline__ bool solve_small(double (&M)[N][N], double (&r)[N], d
       r[c] = sw ? b : a;
       r[i] = sw ? a : b;
     }
-    inv[c] = 1.0 / M[c][c];   // one division a pivot: the chain is all latency
+    if (!PLAIN) inv[c] = 1.0 / M[c][c];
 #pragma unroll
     for (int i = c + 1; i < N; ++i) {
-      const double f = M[i][c] * inv[c];
+      const double f = PLAIN ? M[i][c] / M[c][c] : M[i][c] * inv[c];
 #pragma unroll
-      for (int j = c + 1; j < N; ++j) M[i][j] -= f * M[c][j];
-      r[i] -= f * r[c];
+      for (int j = c + 1; j < N; ++j) M[i][j] = PLAIN ? M[i][j] - f * M[c][j] : fma(-f, M[c][j], M[i][j]);
+      r[i] = PLAIN ? r[i] - f * r[c] : fma(-f, r[c], r[i]);
     }
   }
 #pragma unroll
   for (int c = N - 1; c >= 0; --c) {
     double v = r[c];
 #pragma unroll
-    for (int j = c + 1; j < N; ++j) v -= M[c][j] * x[j];
-    x[c] = v * inv[c];
+    for (int j = c + 1; j < N; ++j) v = PLAIN ? v - M[c][j] * x[j] : fma(-M[c][j], x[j], v);
+    x[c] = PLAIN ? v / M[c][c] : v * inv[c];
     ok = ok && isfinite(x[c]);
   }
   return ok;
@@ -137,7 +142,7 @@ __device__ void fit_step(FitState &s, const double *sums, int i, int max_iter) {
 #pragma unroll
       for (int q = p; q < 3; ++q) M[p][q] = M[q][p] = sums[k++];
     }
-    s.cost_ok = solve_small<3>(M, r, c);
+    s.cost_ok = solve_small<3, true>(M, r, c);
 #pragma unroll
     for (int p = 0; p < 3; ++p) s.c[p] = s.cost_ok ? c[p] : 0.0;
     adopt(s, sums);
@@ -179,7 +184,7 @@ __device__ void fit_step(FitState &s, const double *sums, int i, int max_iter) {
   }
 #pragma unroll
   for (int p = 0; p < 4; ++p) A[p][p] += s.lam * (A[p][p] > 1e-300 ? A[p][p] : 1e-300);
-  if (!solve_small<4>(A, b, d)) {   // singular: every tau clamped, or no data
+  if (!solve_small<4, false>(A, b, d)) {   // singular: every tau clamped, or no data
     s.done = 1;
     return;
   }

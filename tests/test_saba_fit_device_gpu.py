@@ -62,3 +62,18 @@ def test_step_limits():
         assert last is None or a["gain_sse"] <= last
         last = a["gain_sse"]
     assert full["gain_sse"] <= last
+
+
+@pytest.mark.parametrize("rounds,count,prefix", [(1, 4, 777), (200, 31, 1003), (129, 16, 4095),
+                                                 (50, 64, 333), (3046, 8, 1001),
+                                                 (200, 1, None), (3046, 1, None)])
+def test_cost_of_a_log_that_does_not_determine_it(rounds, count, prefix):
+    """Logs of one prefix length, or of one budget: a column of [1, B, B prefix] is a
+    multiple of another, and of these sums (whole numbers, exact in fp64) elimination
+    leaves a zero pivot, so the cost is reported as zero and not as noise."""
+    r = S.gen_replay(rounds, grid=tuple(range(33, 33 + 8 * count, 8)), noise=0.05, seed=count)
+    if prefix:
+        r["prefix"][:] = prefix
+    got = fit(r, (10.0, 20.0, 20.0, 20.0), 5)
+    assert got["c"] == [0.0, 0.0, 0.0] and got["cost_sse"] == 0.0
+    assert np.isfinite(got["phi"]).all()
