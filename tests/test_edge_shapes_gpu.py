@@ -34,12 +34,10 @@ def test_edge_shapes(K, m, center):
     a = ctx.build_tree(x, root, root, fixed_budget=fixed, edges=True)
     b = ctx.build_tree(x[:few].contiguous(), root[:few].clone(), root[:few].clone(),
                        fixed_budget=fixed[:few].clone(), edges=True)
-    # (the logits pass has other block shapes at 1032 rows than at 24, and the last
-    # bit of log q may differ between them: depths whose log q agree are compared)
+    # (rows of one vector a lane have one block shape in the logits pass, 24 or 1032)
     assert torch.equal(a.topk_ids[:few], b.topk_ids)
-    same = (a.topk_logq[:few] == b.topk_logq).all(-1)
-    assert same.float().mean() > 0.3
-    assert torch.equal(a.edge_scores[:few][same], b.edge_scores[same])
+    assert torch.equal(a.topk_logq[:few], b.topk_logq)
+    assert torch.equal(a.edge_scores[:few], b.edge_scores)
     D = torch.float64
     P, C, ud = emb.to(D) @ gp.to(D), emb.to(D) @ gc.to(D), u.to(D)
     ids = a.topk_ids.long()
