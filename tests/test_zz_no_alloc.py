@@ -82,8 +82,9 @@ def test_static_equals_workspace_two_calls_then_smaller():
 
 def test_static_at_the_largest_workload():
     """Workload 4 (batch 128, L 32, V 151936, K 32): about 18 MB of the 24 MiB
-    array; then workload 0 (one sequence, split rows: the split-row partials
-    are carved from the array too) on a second context of the same GPU."""
+    array; then workload 1 (one sequence of 16 rows of 151936 words, each split over
+    16 blocks: the split-row partials are carved from the array too) on a second
+    context of the same GPU."""
     w = S.workload(4)
     sc, sp = WL.scorer_inputs(w, "paper"), WL.saba_inputs(w)
     ctx = WL.gpu_context(w, sc, sp, torch)
@@ -92,11 +93,11 @@ def test_static_at_the_largest_workload():
     _same(_build(ctx, inp, True), _build(ctx, inp, False))
     assert ctx.device_status() == 0
     ctx.close()
-    w0 = S.workload(0)
-    ctx0 = WL.gpu_context(w0, WL.scorer_inputs(w0, "literal"), None, torch)
-    inp0 = _inputs(w0, 0, 1)
-    _same(_build(ctx0, inp0, True), _build(ctx0, inp0, False))
-    ctx0.close()
+    w1 = S.workload(1)
+    ctx1 = WL.gpu_context(w1, WL.scorer_inputs(w1, "literal"), None, torch)
+    inp1 = _inputs(w1, 0, 1)
+    _same(_build(ctx1, inp1, True), _build(ctx1, inp1, False))
+    ctx1.close()
 
 
 def test_static_rejects_a_batch_beyond_the_array():
