@@ -385,7 +385,9 @@ def run_workload(wid, steps, warmup, rotate, hidden_dim, torch, dev, chain=None)
     log("workload %d: per-event stream cost %.4f ms; stages net of it %s" %
         (wid, event_ms, ["%.4f" % x for x in stage_net]))
     k1_s = stage_net[0] * 1e-3
-    achieved = logit_bytes / k1_s / 1e9 if k1_s > 0 else 0.0
+    # stage 0 reads the hidden states too, when they are passed
+    pass_bytes = logit_bytes + (w.batch * w.L * hidden_dim * 2 if hidden_dim else 0)
+    achieved = pass_bytes / k1_s / 1e9 if k1_s > 0 else 0.0
 
     # a plain read of the same rotating buffers, back to back: the streaming
     # read rate the logits pass is compared with
@@ -402,7 +404,7 @@ def run_workload(wid, steps, warmup, rotate, hidden_dim, torch, dev, chain=None)
     read_gbs = logit_bytes / (read_us * 1e-6) / 1e9
     log("workload %d: plain read of one logits buffer: %.2f us = %.0f GB/s" % (wid, read_us, read_gbs))
     return dict(w=w, inp=inp, sc=sc, sp=sp, ctx=ctx, tb=tb, bufs=bufs, R=R,
-                logit_bytes=logit_bytes, ms_per_step=ms_per_step, ms_events=ms_events,
+                logit_bytes=logit_bytes, pass_bytes=pass_bytes, ms_per_step=ms_per_step, ms_events=ms_events,
                 stage_avg=stage_avg, stage_net=stage_net, event_ms=event_ms, achieved=achieved,
                 read_us=read_us, read_gbs=read_gbs, acc_len=acc_len, acc_nodes=acc_nodes,
                 node_mode=node_mode)
@@ -490,7 +492,7 @@ def main():
                        torch, dev)
     w, ctx, tb = run["w"], run["ctx"], run["tb"]
     bufs, R = run["bufs"], run["R"]
-    logit_bytes = run["logit_bytes"]
+    logit_bytes, pass_bytes = run["logit_bytes"], run["pass_bytes"]
     ms_per_step, ms_events = run["ms_per_step"], run["ms_events"]
     stage_avg, stage_net, event_ms = run["stage_avg"], run["stage_net"], run["event_ms"]
     achieved, read_gbs = run["achieved"], run["read_gbs"]
@@ -605,7 +607,7 @@ def main():
             "unit": "GB/s",
             "frac": achieved / HBM_PEAK_GBS,
             "traffic": traffic,
-            "algorithmic_bytes_per_launch": logit_bytes,
+            "algorithmic_bytes_per_launch": pass_bytes,
             "plain_read_gbs": read_gbs,
             "frac_of_plain_read": achieved / read_gbs if read_gbs > 0 else None,
             "kernel_us": 1e3 * stage_net[0],
