@@ -26,13 +26,13 @@
 // Measured against four-wave blocks with sorted thresholds, rows split to reach
 // 1024 blocks and a one-wave merge (rocprofv3, pass plus merge, us):
 //   rows x V, K            before        now
-//   8 x 32000, 4           7.4 + 4.8     9.6
-//   16 x 151936, 8         10.0 + 12.6   9.3 + 4.0
-//   60 x 70001, 13         11.9 + 9.1    13.5
-//   256 x 151936, 8        22.8 + 4.7    21.1
-//   512 x 151936, 64       47.4 + 5.3    37.7
-//   1024 x 128256, 16      45.3          45.4
-//   4096 x 151936, 32      203.7         197.2
+//   8 x 32000, 4           7.6 + 4.3     9.0
+//   16 x 151936, 8         10.3 + 13.3   8.0 + 4.6
+//   60 x 70001, 13         12.3 + 9.4    13.7
+//   256 x 151936, 8        22.8 + 4.4    20.4
+//   512 x 151936, 64       45.7 + 5.4    39.1
+//   1024 x 128256, 16      46.8          46.7
+//   4096 x 151936, 32      202.5         197.9
 #include <algorithm>
 #include <type_traits>
 

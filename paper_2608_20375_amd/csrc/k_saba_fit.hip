@@ -27,7 +27,7 @@
 // 0.1 GFLOP of fp64 an evaluation; a launch takes 8.7 us, of it 1.7 for the last
 // launch's sums, 1.4 for the step, 2.7 for the rounds and 1.4 for the block's
 // sums.  One wave a round with 25 sums a lane, a reducing kernel and the step on
-// the host took 18.9 + 5.2 us and a round trip: that fit 3407 us, this one 903.
+// the host took 18.9 + 5.2 us and a round trip: that fit 3407 us, this one 890.
 // (Rows of 16 lanes a round: 9.0 us a launch; blocks of four waves: 10.2.)
 #include <type_traits>
 

@@ -32,9 +32,9 @@
 //   the block's sum at a time, which keeps its fp32 rounding below that of one long
 //   chain (G = P = 4096: 2.3e-7 of the gradient's norm in one chain, 2.1e-7 so);
 //   per-block partials.
-// G = P = 4096, E = 128, m = 32, K = 16 (us): loss 28.6 -> 25.9, wgrad 22.0 (K rows
-//   a group, a tile of rows a wave, waves summed through LDS) -> 9.9, step 52.4 ->
-//   38.6; G = P = 512, E = 64, m = 16, K = 8: wgrad 8.6 -> 4.4, step 23.3 -> 18.9.
+// G = P = 4096, E = 128, m = 32, K = 16 (us): loss 27.8 -> 25.8, wgrad 22.1 (K rows
+//   a group, a tile of rows a wave, waves summed through LDS) -> 10.5, step 52.5 ->
+//   39.0; G = P = 512, E = 64, m = 16, K = 8: wgrad 8.8 -> 4.1, step 23.1 -> 17.5.
 // update_kernel: sums every partial in fp64 in a fixed order (a step is
 //   deterministic), then applies AdamW to every parameter.
 #include <cmath>
