@@ -46,8 +46,10 @@ SHAPES = [
     (1, 2, 40000, 64, "equal"),
     (27, 19, 9000, 5, "equal"),
     (1, 2, 120000, 48, "equal"),        # split: every partial list is a tie
+    (257, 1, 196625, 40, "equal"),
     (1, 3, 20011, 64, "levels"),        # four values only
     (1, 3, 120011, 17, "levels"),
+    (65, 1, 147473, 24, "levels"),
     (1, 3, 16384, 4, "ordered"),        # the largest logits in one wave's share, most
     (2, 3, 8000, 64, "ordered"),        # of them in a few lanes: one tile a wave
     (27, 19, 8191, 40, "ordered"),
@@ -125,6 +127,7 @@ MASKED = [
     (27, 19, 9001, 8),       # streamed, 4 waves
     (1, 3, 98311, 32),       # split, a tile a wave
     (32, 1, 131080, 16),     # split, streamed; the last split has a wave without a tile
+    (257, 1, 196625, 24),    # split in three, 4 waves
 ]
 
 
