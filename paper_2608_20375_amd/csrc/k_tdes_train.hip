@@ -35,6 +35,11 @@
 // G = P = 4096, E = 128, m = 32, K = 16 (us): loss 27.8 -> 25.8, wgrad 22.1 (K rows
 //   a group, a tile of rows a wave, waves summed through LDS) -> 10.5, step 52.5 ->
 //   39.0; G = P = 512, E = 64, m = 16, K = 8: wgrad 8.8 -> 4.1, step 23.1 -> 17.5.
+//   Score dims that fill no tile (staged by single entries) and more than 16 children
+//   (their embedding rows gathered twice), steps of G = P = 512 and 4096: E = 64, K =
+//   16, m = 20 30.2 -> 24.4 and 40.2 -> 32.7, m = 40 37.9 -> 29.4 and 50.5 -> 39.3; E =
+//   128, m = 32, K = 32 40.0 -> 30.1 and 72.2 -> 47.5, K = 64 51.3 -> 41.5 and 104.8 ->
+//   66.2.
 // update_kernel: sums every partial in fp64 in a fixed order (a step is
 //   deterministic), then applies AdamW to every parameter.
 #include <cmath>
